@@ -289,7 +289,6 @@ int build_descs(const peat_mixed_pair_t *pairs, int32_t count, std::vector<SigDe
             const int64_t nch = (sd.n + (int64_t(1) << sd.chunk_log2) - 1) >> sd.chunk_log2;
             sd.first_chunk = total;
             sd.nchunks = (int32_t)nch;
-            sd.aligned = ((reinterpret_cast<uintptr_t>(sd.g) | reinterpret_cast<uintptr_t>(sd.t)) & 15) == 0;
             total += nch;
         }
     }
@@ -889,7 +888,6 @@ int signature_noalloc_core(const peat_pair_t *pairs, int32_t count, const peat_b
         int64_t &cur = cursor[kind * kClasses + (kMaxChunkLog2 - sd.chunk_log2)];
         sd.first_chunk = cur;
         cur += sd.nchunks;
-        sd.aligned = ((reinterpret_cast<uintptr_t>(sd.g) | reinterpret_cast<uintptr_t>(sd.t)) & 15) == 0;
         if (b.count == kFillDescs || k + 1 == count) {
             hipLaunchKernelGGL(noalloc_fill, dim3((unsigned)b.count), dim3(kBlock), 0, s, b, d_desc, d_map);
             HIP_OR_FAIL(hipGetLastError());

@@ -63,7 +63,7 @@ struct SigDesc {                 // one per pair (48 bytes)
     int16_t dtype;               // golden type
     int16_t tdtype;              // test type
     int32_t chunk_log2;
-    int32_t aligned;             // both pointers 16-byte aligned
+    int32_t reserved;
 };
 static_assert(sizeof(SigDesc) == 48, "SigDesc layout");
 
@@ -209,7 +209,12 @@ struct TopkParams {
 // One launch per kind present: chunks of each kind form one contiguous range
 // [range[kind], range[kind + 1]) of the global chunk numbering.
 hipError_t launch_sig_chunks(const SigParams &p, const int64_t range[kKinds + 1], hipStream_t s);
-hipError_t launch_sig_mixed_kind(const SigParams &p, int kind, int64_t nchunks, hipStream_t s);
+// (the kinds' own launchers; inj: one InjDesc per pair, or NULL)
+hipError_t launch_sig_f32(const SigParams &p, int64_t nchunks, const InjDesc *inj, hipStream_t s);
+hipError_t launch_sig_f16(const SigParams &p, int64_t nchunks, const InjDesc *inj, hipStream_t s);
+hipError_t launch_sig_bf16(const SigParams &p, int64_t nchunks, const InjDesc *inj, hipStream_t s);
+hipError_t launch_sig_mixed(const SigParams &p, int kind, int64_t nchunks, hipStream_t s);
+hipError_t launch_sig_mixed_f64(const SigParams &p, int kind, int64_t nchunks, hipStream_t s);
 // Pass 1 of the same-type kinds with the test tensors' bit flips injected
 // first (inj: one InjDesc per pair, device); the records carry flip counts.
 hipError_t launch_sig_chunks_inject(const SigParams &p, const int64_t range[kKinds + 1], const InjDesc *inj,

@@ -1,7 +1,7 @@
 // Pass 1 of the error signature (sig_chunk) for gfx950, templated on the
 // golden and test element types; included by the translation units that
-// instantiate it (same-type pairs in signature.hip, mixed-precision pairs in
-// mixed.hip).  Pass 2 (sig_finalize, in signature.hip) combines a pair's
+// instantiate it (sig_f32.hip, sig_f16.hip, sig_bf16.hip, mixed.hip,
+// mixed_f64.hip).  Pass 2 (sig_finalize, in signature.hip) combines a pair's
 // chunk records in a fixed order and writes the peat_signature_t.
 //
 // 256-thread blocks, each streaming one or two consecutive fixed-size chunks
@@ -21,13 +21,14 @@
 // mixed pairs, the precision comparisons of Section III-C (the ULP distance
 // counted in the narrower format).
 //
-// Fast path.  A wave whose current vectors hold only "ordinary" pairs (both
-// finite, no NaN, golden nonzero, same sign, relative error below 0.5) needs
-// no classification:
+// Fast path.  "Ordinary" pairs (both finite, no NaN, same sign, relative error
+// below 0.25, or both sides the same zero) need no classification:
 //   - one comparison of the relative error per element flags every other
-//     case (a sign change or a zero golden gives a relative error >= 1 or
-//     NaN) together with the candidates for the maximum relative error; the
-//     exact IEEE quotient is formed only for those candidates;
+//     case (a sign change gives a relative error >= 1) together with the
+//     candidates for the maximum relative error; the exact IEEE quotient is
+//     formed only for those candidates;
+//   - a zero golden gives Inf or NaN there; only then are zeros looked for and
+//     the vector's relative errors formed again without them;
 //   - reciprocals come from one hardware estimate per four (or two) elements
 //     plus a Newton step;
 //   - the maxima of |err| and of the ULP distance are wave-uniform running
@@ -35,10 +36,12 @@
 //     on the spot, while its values are in registers;
 //   - counts use wave ballots; the histogram uses lane-private 16-bit LDS
 //     counters addressed through a binary64-exponent -> row table.
-// Any other vector is deferred: its wave-uniform vector number goes to a
-// per-wave LDS list and the generic per-element path (every IEEE case)
-// processes the list out of the hot loop.  Ragged tails and unaligned pairs
-// use the generic path directly.
+// A vector with any other element is deferred: its wave-uniform vector number
+// goes to a per-wave LDS list, worked out of the hot loop one element per lane
+// and step.  There the ordinary elements are accumulated as on the fast path
+// and only the others are collected, 64 at a time, for the generic path
+// (every IEEE case).  A ragged chunk's last elements, less than one vector per
+// lane, take the same way.
 //
 // Determinism: the element -> lane mapping, per-lane order and the wave
 // reductions of the sums depend only on the chunk size, which depends only on
@@ -89,11 +92,15 @@ constexpr int64_t kGroupElems = int64_t(1) << 19;
 // a lane's 16-bit histogram counters hold a whole run of chunks
 static_assert(kMaxGroup * (int64_t(1) << kMaxChunkLog2) / kBlock < 65536, "histogram counter width");
 constexpr int kHistCols = kBlock / 2;     // histogram words per slot
+constexpr int kElemCap = 128;             // elements for the generic path: < 64 left over + one step's 64
 // the injection's candidate queues fit in the histogram's LDS
 static_assert(sizeof(uint32_t) * kWaves * kQCap <= sizeof(uint32_t) * kHistSlots * kHistCols, "queue size");
 
 __device__ __forceinline__ uint32_t hist_col(int tid) { return (uint32_t)tid & (kHistCols - 1); }
-__device__ __forceinline__ uint32_t hist_inc(int tid) { return tid < kHistCols ? 1u : 0x10000u; }
+// (the same for every lane of a wave: kept in a scalar register)
+__device__ __forceinline__ uint32_t hist_inc(int tid) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)tid) < (uint32_t)kHistCols ? 1u : 0x10000u;
+}
 
 // super-step unroll: lane vectors per tensor per lane
 template <int DG, int DT>
@@ -120,48 +127,91 @@ __device__ __forceinline__ double recip(double b) {
     return __builtin_fma(y, __builtin_fma(-b, y, 1.0), y);
 }
 
-// Reciprocals of four magnitudes from one reciprocal of their product (the
-// hardware reciprocal issues at a quarter of the fma rate).  The inputs are
-// widened f32/f16/bf16 golden values (the golden side is never binary64), so
-// the product of four stays a normal binary64 number (between 2^-600 and
-// 2^512) and the pairwise products are exact; each result is within a few
-// units of 2^-48 of 1/x.  A zero, Inf or NaN among the four makes all four
-// results NaN or Inf.
-__device__ __forceinline__ void recip4(const double *x, double *r) {
-    const double p01 = x[0] * x[1], p23 = x[2] * x[3];
-    const double inv = recip(p01 * p23);
-    const double i01 = inv * p23, i23 = inv * p01;
-    r[0] = x[1] * i01;
-    r[1] = x[0] * i01;
-    r[2] = x[3] * i23;
-    r[3] = x[2] * i23;
+// Reciprocals of a lane vector's magnitudes from one reciprocal of their
+// product (the hardware reciprocal issues at a quarter of the fma rate), in
+// two parts: the products and the back-multiplication.  The inputs are widened f32/f16/bf16 golden
+// values (the golden side is never binary64), so the product of four stays a
+// normal binary64 number (between 2^-600 and 2^512) and the pairwise products
+// are exact; each result is within a few units of 2^-48 of 1/x.  A zero, Inf or
+// NaN among them makes all results NaN or Inf.  Eight only for f16 values (in
+// [2^-24, 2^16]: products within [2^-192, 2^128]): the pair and quad products
+// are exact (at most 44 significant bits) and only the product of all eight
+// rounds, so each result is within about 2^-47.8 of 1/x.
+template <int N> struct Prod;
+template <> struct Prod<2> {
+    double all;
+    __device__ __forceinline__ explicit Prod(const double *x) : all(x[0] * x[1]) {}
+    __device__ __forceinline__ void recips(const double *x, double *r) const {
+        const double inv = recip(all);
+        r[0] = x[1] * inv;
+        r[1] = x[0] * inv;
+    }
+};
+template <> struct Prod<4> {
+    double p01, p23, all;
+    __device__ __forceinline__ explicit Prod(const double *x) : p01(x[0] * x[1]), p23(x[2] * x[3]), all(p01 * p23) {}
+    __device__ __forceinline__ void back(const double *x, double *r, double inv) const {
+        const double i01 = inv * p23, i23 = inv * p01;
+        r[0] = x[1] * i01;
+        r[1] = x[0] * i01;
+        r[2] = x[3] * i23;
+        r[3] = x[2] * i23;
+    }
+    __device__ __forceinline__ void recips(const double *x, double *r) const { back(x, r, recip(all)); }
+};
+template <> struct Prod<8> {
+    Prod<4> a, b;
+    double all;
+    __device__ __forceinline__ explicit Prod(const double *x) : a(x), b(x + 4), all(a.all * b.all) {}
+    __device__ __forceinline__ void recips(const double *x, double *r) const {
+        const double inv = recip(all);
+        a.back(x, r, inv * b.all);
+        b.back(x + 4, r + 4, inv * a.all);
+    }
+};
+// Reciprocals of VEC golden magnitudes in groups of N.
+template <int VEC, int N>
+__device__ __forceinline__ void recip_golden(const double *x, double *r) {
+#pragma unroll
+    for (int q = 0; q < VEC; q += N) Prod<N>(x + q).recips(x + q, r + q);
 }
-// The same for two magnitudes (lane vectors of two elements).
-__device__ __forceinline__ void recip2(const double *x, double *r) {
-    const double inv = recip(x[0] * x[1]);
-    r[0] = x[1] * inv;
-    r[1] = x[0] * inv;
+
+// A rectifier's output has a zero golden in nearly every vector, so this is
+// part of the fast path and not of the deferred one.  It is looked for only
+// when a relative error is rare, which costs vectors without zeros nothing
+// (one test per reciprocal in the hot path cost the FP32/FP16 kernel 5 %).
+// Relative errors of a vector in which some golden is zero (G the goldens, E
+// the errors, same(j): golden and test of element j have the same bits).  A
+// zero golden makes all the reciprocals it shares a product with NaN or Inf,
+// so they are formed again with zeros replaced by the type's smallest
+// magnitude, which leaves every other value as it is.  A zero golden is
+// ordinary when the test is the same zero (relative error 0 here, and counted
+// out of the relative errors by nz), else not (1).
+template <int DG, int VEC, int N, typename F>
+__device__ __forceinline__ void zero_rel(const double *G, const double *E, double *R, uint32_t &nz, F &&same) {
+    constexpr double kLeast = DG == PEAT_F16 ? 0x1p-24 : 0x1p-149;
+#pragma unroll
+    for (int q = 0; q < VEC; q += N) {
+        double y[N], r[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) y[j] = __builtin_fmax(__builtin_fabs(G[q + j]), kLeast);
+        Prod<N>(y).recips(y, r);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const bool z = G[q + j] == 0.0;
+            const bool odd = z && !same(q + j);
+            R[q + j] = odd ? 1.0 : __builtin_fabs(E[q + j]) * r[j];
+            nz += wave_count(z && !odd);
+        }
+    }
 }
-// Eight magnitudes of widened f16 values (in [2^-24, 2^16]) from one
-// reciprocal: the product of eight stays within [2^-192, 2^128]; the pair
-// and quad products are exact (at most 44 significant bits) and only the
-// product of all eight rounds, so each result is within about 2^-47.8 of
-// 1/x.  A zero, Inf or NaN among the eight makes all eight NaN or Inf.
-__device__ __forceinline__ void recip8(const double *x, double *r) {
-    const double p01 = x[0] * x[1], p23 = x[2] * x[3], p45 = x[4] * x[5], p67 = x[6] * x[7];
-    const double q0 = p01 * p23, q1 = p45 * p67;
-    const double inv = recip(q0 * q1);
-    const double iq0 = inv * q1, iq1 = inv * q0;
-    const double i01 = iq0 * p23, i23 = iq0 * p01, i45 = iq1 * p67, i67 = iq1 * p45;
-    r[0] = x[1] * i01;
-    r[1] = x[0] * i01;
-    r[2] = x[3] * i23;
-    r[3] = x[2] * i23;
-    r[4] = x[5] * i45;
-    r[5] = x[4] * i45;
-    r[6] = x[7] * i67;
-    r[7] = x[6] * i67;
-}
+
+// End of a wave-uniform block that holds lane-dependent branches: their paths
+// join here, so that the block's own join merges uniform values only.
+// Without it the compiler joins both in one place, takes every value merged
+// there for lane-dependent (vector registers) and every branch on one of them
+// for a divergent branch.
+__device__ __forceinline__ void join_uniform() { __builtin_amdgcn_wave_barrier(); }
 
 struct Lane {
     double s_abs, s_rel;           // both paths
@@ -170,13 +220,15 @@ struct Lane {
     uint32_t gi_abs;
     uint32_t gu, gi_ulp;           // both paths: max ULP and element index
     double mx_rel;                 // both paths: max rel err and its index
-    double rthr;                   // fast-path filter, at most kRareRel
     uint32_t ix_rel;
     uint64_t s_ulp;
     uint32_t s_ulp32;              // fast path: ULP sum of the current super-step
     uint32_t first_nan, first_valid;
-    uint32_t cnt[kCnt];                    // generic-path counts (per lane)
-    uint32_t mism[PEAT_MAX_THRESHOLDS];    // generic-path mismatches (per lane)
+    // generic-path counts and mismatches of the lane, two 16-bit counters per
+    // word (a lane takes at most about 8192 elements per run)
+    uint32_t cnt[kCnt / 2];
+    uint32_t mism[PEAT_MAX_THRESHOLDS / 2];
+    __device__ __forceinline__ void count(int c, uint32_t by) { cnt[c / 2] += by << (16 * (c & 1)); }
 };
 
 // Fast-path state shared by the wave.  Vectors reach the fast path in
@@ -186,6 +238,10 @@ struct Lane {
 // element equal to the running maximum in a later vector cannot.
 struct Uni {
     uint32_t common;                       // ordinary vectors per lane
+    uint32_t single;                       // ordinary elements of deferred vectors and ragged rests
+    uint32_t zeros;                        // ordinary elements whose golden is zero
+    uint32_t ready;                        // the filter holds a value >= 0
+    double rthr;                           // max relative error filter, at most kRareRel
     uint32_t mism[PEAT_MAX_THRESHOLDS];
     uint32_t first;                        // first ordinary vector number
     double wx_abs;                         // running max |err|
@@ -200,6 +256,7 @@ struct alignas(16) Shared {
     // counts at most 2^18 / 256 = 1024 elements per chunk, so no half carries.
     uint32_t hist[kHistSlots * kHistCols];
     uint32_t defer[kWaves][kDeferCap];     // deferred vector numbers per wave
+    uint32_t elems[kWaves][kElemCap];      // element indices (within the chunk) for the generic path
     // generic-path sums of a^2, g^2, t^2 and g*t, one column per lane
     double gsum[4][kBlock];
     double rd[kWaves][6];
@@ -247,16 +304,16 @@ __device__ __forceinline__ void lane_init(Lane &L, Uni &U) {
     L.gu = 0;
     L.gi_ulp = kNone;
     L.mx_rel = -1.0;
-    L.rthr = -1.0;
     L.ix_rel = kNone;
     L.s_ulp = 0;
     L.s_ulp32 = 0;
     L.first_nan = L.first_valid = kNone;
 #pragma unroll
-    for (int c = 0; c < kCnt; ++c) L.cnt[c] = 0;
+    for (int c = 0; c < kCnt / 2; ++c) L.cnt[c] = 0;
 #pragma unroll
-    for (int j = 0; j < PEAT_MAX_THRESHOLDS; ++j) L.mism[j] = 0;
-    U.common = 0;
+    for (int j = 0; j < PEAT_MAX_THRESHOLDS / 2; ++j) L.mism[j] = 0;
+    U.rthr = -1.0;
+    U.common = U.single = U.zeros = U.ready = 0;
     U.first = kNone;
     U.wx_abs = -1.0;
     U.wu = 0;
@@ -308,16 +365,16 @@ __device__ __forceinline__ void generic_elem(Lane &L, GenAcc &ga, Shared &sh, co
     const double G = widen<DG>(gb), T = widen<DT>(tb);
     const bool nan_g = G != G, nan_t = T != T;
     const bool inf_g = __builtin_isinf(G), inf_t = __builtin_isinf(T);
-    L.cnt[C_NAN_G] += nan_g;
-    L.cnt[C_NAN_T] += nan_t;
-    L.cnt[C_INF_G] += inf_g;
-    L.cnt[C_INF_T] += inf_t;
+    L.count(C_NAN_G, nan_g);
+    L.count(C_NAN_T, nan_t);
+    L.count(C_INF_G, inf_g);
+    L.count(C_INF_T, inf_t);
     if (nan_g || nan_t) {
-        L.cnt[C_NANPAIR] += 1;
+        L.count(C_NANPAIR, 1);
         L.first_nan = min(L.first_nan, li);
         return;
     }
-    L.cnt[C_VALID] += 1;
+    L.count(C_VALID, 1);
     L.first_valid = min(L.first_valid, li);
     const double a = (G == T) ? 0.0 : __builtin_fabs(T - G);
     // ULP distance in the narrower format (the wider value rounded to it)
@@ -350,27 +407,26 @@ __device__ __forceinline__ void generic_elem(Lane &L, GenAcc &ga, Shared &sh, co
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const double allowed = P.any_rtol ? __dadd_rn(P.thr[j], __builtin_fabs(__dmul_rn(P.rthr[j], G))) : P.thr[j];
-        L.mism[j] += (a != 0.0) && (ainf || !(a <= allowed));
+        L.mism[j / 2] += ((a != 0.0) && (ainf || !(a <= allowed)) ? 1u : 0u) << (16 * (j & 1));
     }
     if (a > L.gx_abs || (a == L.gx_abs && li < L.gi_abs)) {
         L.gx_abs = a;
         L.gi_abs = li;
     }
     if (inf_g || inf_t) return;
-    L.cnt[C_FINITE] += 1;
+    L.count(C_FINITE, 1);
     L.s_abs += a;
     ga.sq = __builtin_fma(a, a, ga.sq);
     ga.g2 = __builtin_fma(G, G, ga.g2);
     ga.t2 = __builtin_fma(T, T, ga.t2);
     ga.gt = __builtin_fma(G, T, ga.gt);
     if (G != 0.0) {
-        L.cnt[C_REL] += 1;
+        L.count(C_REL, 1);
         const double r = a / __builtin_fabs(G);
         L.s_rel += r;
         if (r > L.mx_rel || (r == L.mx_rel && li < L.ix_rel)) {
             L.mx_rel = r;
             L.ix_rel = li;
-            L.rthr = __builtin_fmin(r - r * kRelMargin, kRareRel);
         }
     }
 }
@@ -497,8 +553,8 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // vector after lane_init that is not rare: its relative errors all exceed the
 // initial filter of -1, so every lane's filter becomes the wave's maximum
 // (>= 0) less the margin, and max |err| becomes >= 0; later updates (here or
-// in generic_elem) only store values >= 0.  That vector is also the first
-// ordinary one counted since lane_init, so the test is a nonzero count (a
+// in generic_elem) only store values >= 0.  A vector whose goldens are all
+// zero has no relative error, so U.ready tells when the filter is set (a
 // scalar compare).
 // With no negative absolute tolerance a zero error is close under every
 // threshold (the allowance atol + |rtol g| is at least atol >= 0).  What is
@@ -539,7 +595,7 @@ __device__ __forceinline__ bool vec_fast16(Lane &L, Uni &U, Shared &sh, const Si
         __builtin_elementwise_max(__builtin_bit_cast(u16x2, d[2]), __builtin_bit_cast(u16x2, d[3])));
     const uint32_t vu = max((uint32_t)dm.x, (uint32_t)dm.y);
     // (laid out as the taken branch: the full path falls through)
-    if (__builtin_expect(U.common != 0 && P.thr_min >= 0.0 && __ballot(vu != 0u) == 0, 0)) {
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(U.ready) != 0 && P.thr_min >= 0.0 && __ballot(vu != 0u) == 0, 0)) {
         const float q0 = (G32[0] * G32[1]) * (G32[2] * G32[3]);
         const float q1 = (G32[4] * G32[5]) * (G32[6] * G32[7]);
         // class test: NaN, infinite, zero or subnormal (every class but normal)
@@ -576,16 +632,13 @@ __device__ __forceinline__ bool vec_fast16(Lane &L, Uni &U, Shared &sh, const Si
         E[j] = (double)E32[j];
         AG[j] = __builtin_fabs(G[j]);
     }
-    if constexpr (DT == PEAT_F16) {
-        recip8(AG, IG);
-    } else {
-        recip4(AG, IG);
-        recip4(AG + 4, IG + 4);
-    }
+    constexpr int N = DT == PEAT_F16 ? 8 : 4;
+    recip_golden<VEC, N>(AG, IG);
+    uint32_t nz = 0;
 #pragma unroll
     for (int j = 0; j < VEC; ++j) {
         R[j] = __builtin_fabs(E[j]) * IG[j];
-        mflag |= __ballot(!(R[j] <= L.rthr));
+        mflag |= __ballot(!(R[j] <= U.rthr));
         row[j] = hist_key(E[j]);                      // the table is read after the branch
     }
     double va = absmax_f64(E[0], E[1]);
@@ -593,19 +646,29 @@ __device__ __forceinline__ bool vec_fast16(Lane &L, Uni &U, Shared &sh, const Si
     for (int j = 2; j < VEC; ++j) va = absmax_f64(va, E[j]);
     mflag |= __ballot(va > U.wx_abs);
     mflag |= __ballot(vu > U.wu);
-    if (mflag != 0) {
+    if (__builtin_expect(mflag != 0, 0)) {
         uint64_t mrare = 0, mcand = 0;
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-            mrare |= __ballot(!(R[j] < kRareRel));
-            mcand |= __ballot(R[j] > L.rthr);
+        for (int j = 0; j < VEC; ++j) mrare |= __ballot(!(R[j] < kRareRel));
+        if (__builtin_expect(mrare != 0, 0)) {
+            uint64_t mz = 0;
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) mz |= __ballot(G[j] == 0.0);
+            if (mz != 0) {
+                zero_rel<DT, VEC, N>(G, E, R, nz, [&](int j) { return ((d[j >> 1] >> (16 * (j & 1))) & 0xFFFFu) == 0u; });
+                mrare = 0;
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) mrare |= __ballot(!(R[j] < kRareRel));
+            }
         }
         if (mrare != 0) return true;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) mcand |= __ballot(R[j] > U.rthr);
         const uint32_t li0 = ib + (v * kBlock + tid) * VEC;
         if (mcand != 0) {
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
-                if (R[j] > L.rthr) {
+                if (R[j] > U.rthr) {
                     const double r = __builtin_fabs(E[j]) / __builtin_fabs(G[j]);   // IEEE quotient
                     if (r > L.mx_rel) {
                         L.mx_rel = r;
@@ -614,7 +677,8 @@ __device__ __forceinline__ bool vec_fast16(Lane &L, Uni &U, Shared &sh, const Si
                 }
             }
             const double wm = wave_max_uniform(L.mx_rel);
-            L.rthr = __builtin_fmin(wm - wm * kRelMargin, kRareRel);
+            U.rthr = __builtin_fmin(wm - wm * kRelMargin, kRareRel);
+            U.ready = wm >= 0.0 ? 1u : 0u;
         }
         if (__ballot(va > U.wx_abs) != 0) {
             U.wx_abs = wave_max_uniform(va);
@@ -625,6 +689,7 @@ __device__ __forceinline__ bool vec_fast16(Lane &L, Uni &U, Shared &sh, const Si
                     if (__builtin_fabs(E[j]) == U.wx_abs) ix = li0 + j;
                 lex_merge(L.gx_abs, L.gi_abs, U.wx_abs, ix);
             }
+            join_uniform();
         }
         if (__ballot(vu > U.wu) != 0) {
             U.wu = wave_max_uniform_u(vu);
@@ -636,6 +701,7 @@ __device__ __forceinline__ bool vec_fast16(Lane &L, Uni &U, Shared &sh, const Si
                 lex_merge(L.gu, L.gi_ulp, U.wu, ix);
             }
         }
+        join_uniform();
     }
 
     {
@@ -660,6 +726,7 @@ __device__ __forceinline__ bool vec_fast16(Lane &L, Uni &U, Shared &sh, const Si
     }
     count_mismatches<VEC, NT, RT>(U, P, E, G, va);
     U.common += 1;
+    U.zeros += nz;
     if (U.first == kNone) U.first = v;
     return false;
 }
@@ -696,12 +763,9 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
         }
         AG[j] = __builtin_fabs(G[j]);
     }
-    if constexpr (VEC == 2) {
-        recip2(AG, IG);
-    } else {
-#pragma unroll
-        for (int q = 0; q < VEC; q += 4) recip4(AG + q, IG + q);
-    }
+    constexpr int N = VEC == 2 ? 2 : 4;
+    recip_golden<VEC, N>(AG, IG);
+    uint32_t nz = 0;
 #pragma unroll
     for (int j = 0; j < VEC; ++j) {
         const auto gb = lane_elem<DG>(gv, j);
@@ -718,7 +782,7 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
         R[j] = __builtin_fabs(E[j]) * IG[j];
         // rare (NaN, or at least kRareRel while the filter is there), or a
         // candidate for the max relative error
-        mflag |= __ballot(!(R[j] <= L.rthr));
+        mflag |= __ballot(!(R[j] <= U.rthr));
         // same sign on the fast path: the ULP distance is |t - g| of the bit patterns
         u[j] = fast_ulp<DG, DT>(gb, tb, G[j], Tj);
         row[j] = hist_key(E[j]);                      // the table is read after the branch
@@ -731,14 +795,29 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
     for (int j = 2; j < VEC; ++j) vu = max(vu, u[j]);
     mflag |= __ballot(va > U.wx_abs);
     mflag |= __ballot(vu > U.wu);
-    if (mflag != 0) {
+    if (__builtin_expect(mflag != 0, 0)) {
         uint64_t mrare = 0, mcand = 0;
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-            mrare |= __ballot(!(R[j] < kRareRel));
-            mcand |= __ballot(R[j] > L.rthr);
+        for (int j = 0; j < VEC; ++j) mrare |= __ballot(!(R[j] < kRareRel));
+        if (__builtin_expect(mrare != 0, 0)) {
+            uint64_t mz = 0;
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) mz |= __ballot(G[j] == 0.0);
+            if (mz != 0) {
+                zero_rel<DG, VEC, N>(G, E, R, nz, [&](int j) {
+                    if constexpr (kDiff32)
+                        return __float_as_uint(widen32<DT>(lane_elem<DT>(tv, j))) == __float_as_uint(G32[j]);
+                    else
+                        return __double_as_longlong(widen<DT>(lane_elem<DT>(tv, j))) == __double_as_longlong(G[j]);
+                });
+                mrare = 0;
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) mrare |= __ballot(!(R[j] < kRareRel));
+            }
         }
         if (mrare != 0) return true;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) mcand |= __ballot(R[j] > U.rthr);
         const uint32_t li0 = ib + (v * kBlock + tid) * VEC;
         if (mcand != 0) {
             // The filter threshold is shared by the wave: an element whose
@@ -749,7 +828,7 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
             // of the chunk.
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
-                if (R[j] > L.rthr) {
+                if (R[j] > U.rthr) {
                     const double r = __builtin_fabs(E[j]) / __builtin_fabs(G[j]);   // IEEE quotient
                     if (r > L.mx_rel) {
                         L.mx_rel = r;
@@ -758,7 +837,8 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
                 }
             }
             const double wm = wave_max_uniform(L.mx_rel);
-            L.rthr = __builtin_fmin(wm - wm * kRelMargin, kRareRel);
+            U.rthr = __builtin_fmin(wm - wm * kRelMargin, kRareRel);
+            U.ready = wm >= 0.0 ? 1u : 0u;
         }
         // A new running maximum: the lanes that hold it record its lowest
         // index in this vector (an equal value in a later vector has a
@@ -773,6 +853,7 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
                     if (__builtin_fabs(E[j]) == U.wx_abs) ix = li0 + j;
                 lex_merge(L.gx_abs, L.gi_abs, U.wx_abs, ix);
             }
+            join_uniform();
         }
         if (__ballot(vu > U.wu) != 0) {
             U.wu = wave_max_uniform_u(vu);
@@ -784,6 +865,7 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
                 lex_merge(L.gu, L.gi_ulp, U.wu, ix);
             }
         }
+        join_uniform();
     }
 
     {
@@ -807,8 +889,75 @@ __device__ __forceinline__ bool vec_fast(Lane &L, Uni &U, Shared &sh, const SigP
     }
     count_mismatches<VEC, NT, RT>(U, P, E, G, va);
     U.common += 1;
+    U.zeros += nz;
     if (U.first == kNone) U.first = v;
     return false;
+}
+
+// One element per lane (on: the lane has one), with its own reciprocal: an
+// ordinary one is accumulated as vec_fast does, with every decision per lane;
+// returns whether it was.  Called with every lane active.
+template <int DG, int DT, int NT, bool RT, typename BG, typename BT>
+__device__ __forceinline__ bool single_elem(Lane &L, Uni &U, Shared &sh, const SigParams &P, BG gb, BT tb, uint32_t li,
+                                            bool on, int tid) {
+    constexpr bool kDiff32 = Tr<DG>::W <= 32 && Tr<DT>::W <= 32;
+    double G, T, E;
+    bool same;                                   // the same bits, once widened
+    if constexpr (kDiff32) {
+        const float g = widen32<DG>(gb), t = widen32<DT>(tb);
+        G = (double)g;
+        T = (double)t;
+        E = (double)(t - g);
+        same = __float_as_uint(g) == __float_as_uint(t);
+    } else {
+        G = widen<DG>(gb);
+        T = widen<DT>(tb);
+        E = T - G;
+        same = __double_as_longlong(G) == __double_as_longlong(T);
+    }
+    const bool zg = G == 0.0;
+    const double a = __builtin_fabs(E);
+    const double R = zg ? (same ? 0.0 : 1.0) : a * recip(__builtin_fabs(G));
+    const bool ord = on && R < kRareRel;
+    U.single += wave_count(ord);
+    U.zeros += wave_count(ord && zg);
+    if (ord) {
+        hist_add(sh, E, tid);
+        const uint32_t u = fast_ulp<DG, DT>(gb, tb, G, T);
+        L.s_ulp += u;
+        L.s_abs += a;
+        L.s_sq = __builtin_fma(E, E, L.s_sq);
+        L.s_g2 = __builtin_fma(G, G, L.s_g2);
+        L.s_ge = __builtin_fma(G, E, L.s_ge);
+        L.s_rel += R;
+        L.first_valid = min(L.first_valid, li);
+        if (u > L.gu || (u == L.gu && li < L.gi_ulp)) {
+            L.gu = u;
+            L.gi_ulp = li;
+        }
+        if (a > L.gx_abs || (a == L.gx_abs && li < L.gi_abs)) {
+            L.gx_abs = a;
+            L.gi_abs = li;
+        }
+    }
+    // (not below the filter: a deferred element may come before the holder of
+    // an equal maximum, also of a maximum of 0, which the margin cannot lower)
+    const bool cand = ord && !zg && R >= U.rthr;
+    if (__ballot(cand) != 0) {
+        if (cand) {
+            const double r = a / __builtin_fabs(G);               // IEEE quotient
+            if (r > L.mx_rel || (r == L.mx_rel && li < L.ix_rel)) {
+                L.mx_rel = r;
+                L.ix_rel = li;
+            }
+        }
+        const double wm = wave_max_uniform(L.mx_rel);
+        U.rthr = __builtin_fmin(wm - wm * kRelMargin, kRareRel);
+        U.ready = wm >= 0.0 ? 1u : 0u;
+    }
+    const double one_e[1] = {ord ? E : 0.0}, one_g[1] = {G};
+    count_mismatches<1, NT, RT>(U, P, one_e, one_g, __builtin_fabs(one_e[0]));
+    return ord;
 }
 
 // ---- wave reductions by DPP (chunk records, finalize) ------------------------
@@ -939,7 +1088,7 @@ struct ChunkCtx {
     int32_t pair;
     int32_t log2;                            // chunk size of the pair
     uint32_t len;                            // elements
-    uint32_t nsuper;                         // full super-steps (0 when unaligned)
+    uint32_t nsuper;                         // full super-steps
 };
 
 // The block's chunks: chunk_group consecutive chunks of the launch, streamed
@@ -971,7 +1120,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
     constexpr int ESZG = Tr<DG>::W / 8, ESZT = Tr<DT>::W / 8;
     constexpr int BG = PT::BG, BT = PT::BT;     // bytes per lane vector
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = (int)__builtin_amdgcn_readfirstlane((uint32_t)tid >> 6), lane = tid & 63;
     const int64_t nch = P.chunk_count;
     const uint32_t lane_off_g = (uint32_t)tid * BG, lane_off_t = (uint32_t)tid * BT;
 
@@ -981,7 +1130,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
     struct PairS {
         const char *g, *t;
         int64_t n, first;
-        int32_t pair, log2, nchunks, aligned;
+        int32_t pair, log2, nchunks;
     };
     auto pair_of = [&](int64_t c) {
         PairS d;
@@ -1001,7 +1150,6 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         d.first = (int64_t)uniform_u64((uint64_t)dm.first_chunk);
         d.log2 = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)dm.chunk_log2);
         d.nchunks = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)dm.nchunks);
-        d.aligned = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)dm.aligned);
         return d;
     };
     auto ctx = [&](const PairS &d, int64_t c) {
@@ -1014,7 +1162,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         x.len = (uint32_t)(rest < (int64_t(1) << d.log2) ? rest : (int64_t(1) << d.log2));
         x.gbase = d.g + x.off * ESZG;
         x.tbase = d.t + x.off * ESZT;
-        x.nsuper = d.aligned != 0 ? x.len / SUPER : 0;
+        x.nsuper = x.len / SUPER;
         return x;
     };
 
@@ -1059,54 +1207,93 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         load_at(g, t, c.gbase, c.tbase, c.len, s);
     };
     // ib: index of the chunk's first element relative to the run
+    auto work = [&](const u32x4 &g, const u32x4 &t, uint32_t v, uint32_t ib) {
+        if (vec_fast<DG, DT, NT, RT>(L, Un, sh, P, g, t, v, ib, tid)) {
+            sh.defer[wave][ndef] = v;          // every lane writes the same value
+            ++ndef;
+        }
+    };
     auto step = [&](const u32x4 (&g)[U], const u32x4 (&t)[U], uint32_t s, uint32_t ib) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t v = s * U + u;
-            if (vec_fast<DG, DT, NT, RT>(L, Un, sh, P, g[u], t[u], v, ib, tid)) {
-                sh.defer[wave][ndef] = v;      // every lane writes the same value
-                ++ndef;
-            }
-        }
+        for (int u = 0; u < U; ++u) work(g[u], t[u], s * U + u, ib);
         // at most U * VEC distances below 2^24 each: no 32-bit overflow
         L.s_ulp += L.s_ulp32;
         L.s_ulp32 = 0;
     };
-    // The deferred vectors of the current chunk through the generic path.
-    auto flush = [&](const ChunkCtx &c, uint32_t ib) {
-        if (ndef != 0) {
-            GenAcc gf;
-            gf.load(sh, tid);
-#pragma unroll 1
-            for (uint32_t k = 0; k < ndef; ++k) {
-                const uint32_t v = sh.defer[wave][k];
-                const u32x4 gv = load_vec<BG>(c.gbase, v * kBlock + tid);
-                const u32x4 tv = load_vec<BT>(c.tbase, v * kBlock + tid);
-                const uint32_t li0 = ib + (v * kBlock + tid) * VEC;
-#pragma unroll 1
-                for (int j = 0; j < VEC; ++j)
-                    generic_elem<DG, DT, NT>(L, gf, sh, P, lane_elem<DG>(gv, j), lane_elem<DT>(tv, j), li0 + j,
-                                             tid);
+    // (Unaligned tensors stream like aligned ones: buffer loads take any byte
+    // address.  16 bf16 pairs of 6.4 M elements at odd offsets, four
+    // tolerances: 608 -> 202 us a call, against 1 element per lane and load
+    // through the generic path before.)
+    // The deferred vectors of the current chunk and, at its end, the elements
+    // from `tail` on: one element per lane and step, each step's loads ahead
+    // of the previous step's work.  Ordinary elements are accumulated here
+    // (their own reciprocal; the decisions and sums of the fast path), the
+    // others are listed and go through the generic path 64 at a time.
+    auto rest = [&](const ChunkCtx &c, uint32_t ib, uint32_t tail, bool end) {
+        const uint32_t kb = ndef * VEC;
+        const uint32_t kc = kb + (end ? (c.len - tail + kBlock - 1) / kBlock : 0u);
+        if (kc == 0) return;
+        uint32_t nel = 0;                        // length of the element list (uniform)
+        auto place = [&](uint32_t k, bool &on) -> uint32_t {
+            if (k < kb) {
+                on = true;
+                return (sh.defer[wave][k / VEC] * kBlock + tid) * VEC + k % VEC;
             }
-            gf.store(sh, tid);
-            ndef = 0;
-            // nothing of the flush stays in flight: the hot loop then waits
-            // only for its own loads
-            __builtin_amdgcn_s_waitcnt(0);
+            const uint32_t li = tail + (k - kb) * kBlock + tid;
+            on = li < c.len;
+            return on ? li : 0u;
+        };
+        bool on;
+        uint32_t li = place(0, on);
+        auto gv = load_elem<DG>(c.gbase, li);
+        auto tv = load_elem<DT>(c.tbase, li);
+#pragma unroll 1
+        for (uint32_t k = 0; k <= kc; ++k) {     // the last step works the rest of the list alone
+            bool non;
+            const uint32_t nli = place(min(k + 1, kc - 1), non);
+            const auto ng = load_elem<DG>(c.gbase, nli);
+            const auto nt = load_elem<DT>(c.tbase, nli);
+            const bool other = on && !single_elem<DG, DT, NT, RT>(L, Un, sh, P, gv, tv, ib + li, on, tid);
+            const uint64_t m = __ballot(other);
+            if (m != 0) {
+                if (other) {
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    sh.elems[wave][nel + rank] = li;
+                }
+                nel += (uint32_t)__popcll(m);
+            }
+            const uint32_t take = nel >= 64 ? 64u : (k == kc ? nel : 0u);
+            if (take != 0) {
+                nel -= take;
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");    // entries of other lanes
+                if ((uint32_t)lane < take) {
+                    const uint32_t e = sh.elems[wave][nel + lane];
+                    GenAcc gf;
+                    gf.load(sh, tid);
+                    generic_elem<DG, DT, NT>(L, gf, sh, P, load_elem<DG>(c.gbase, e), load_elem<DT>(c.tbase, e), ib + e,
+                                             tid);
+                    gf.store(sh, tid);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            }
+            on = non && k + 1 < kc;
+            li = nli;
+            gv = ng;
+            tv = nt;
         }
+        ndef = 0;
+        // nothing of this stays in flight: the hot loop then waits only for
+        // its own loads
+        __builtin_amdgcn_s_waitcnt(0);
     };
 
-    // End of a chunk: the ragged tail (or the whole chunk when a pointer is
-    // not 16-byte aligned) and the wave's binary64 sums.  Fast-path t^2 and
+    // End of a chunk: the wave's binary64 sums.  Fast-path t^2 and
     // g*t come from their exact per-element identities, then the generic
     // path's direct sums are added; a fixed order per lane.
     auto chunk_end = [&](const ChunkCtx &c, uint32_t ib, bool run_end) {
         GenAcc ga;
         ga.load(sh, tid);
-#pragma unroll 1
-        for (uint32_t li = c.nsuper * SUPER + tid; li < c.len; li += kBlock)
-            generic_elem<DG, DT, NT>(L, ga, sh, P, load_elem<DG>(c.gbase, li), load_elem<DT>(c.tbase, li), ib + li,
-                                     tid);
         // the first ordinary element of this lane in the chunk
         if (Un.first != kNone) {
             L.first_valid = min(L.first_valid, ib + (Un.first * kBlock + tid) * VEC);
@@ -1158,16 +1345,17 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
             }
         }
         {
-            // fast-path counts: every element there is valid, finite, golden nonzero
-            const uint32_t common = Un.common * 64u * VEC;
+            // fast-path counts: every element there is valid and finite
+            const uint32_t common = Un.common * 64u * VEC + Un.single;
 #pragma unroll
             for (int k = 0; k < kCnt; ++k) {
-                const uint32_t v = dpp_sum_u32(L.cnt[k]) + ((k == C_VALID || k == C_FINITE || k == C_REL) ? common : 0u);
+                const uint32_t v = dpp_sum_u32((L.cnt[k / 2] >> (16 * (k & 1))) & 0xFFFFu) +
+                                   ((k == C_VALID || k == C_FINITE) ? common : (k == C_REL ? common - Un.zeros : 0u));
                 if (lane == 0) sh.rcnt[wave][k] = v;
             }
 #pragma unroll
             for (int j = 0; j < PEAT_MAX_THRESHOLDS; ++j) {
-                const uint32_t v = j < NT ? dpp_sum_u32(L.mism[j]) + Un.mism[j] : 0u;
+                const uint32_t v = j < NT ? dpp_sum_u32((L.mism[j / 2] >> (16 * (j & 1))) & 0xFFFFu) + Un.mism[j] : 0u;
                 if (lane == 0) sh.rcnt[wave][kCnt + j] = v;
             }
         }
@@ -1347,8 +1535,8 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
                         hop ? 0u : (last && !odd ? s + 1 : s + 2));
                 step(gb, tb, s + 1, ib);
                 // the deferred list must hold the next two super-steps (or the
-                // odd last one)
-                if (ndef > kDeferCap - 2 * U) flush(cur, ib);
+                // odd last one and the ragged rest's vectors)
+                if (ndef > kDeferCap - 2 * U) rest(cur, ib, 0, false);
             }
             if (odd) {
                 step(ga, ta, npair, ib);
@@ -1357,7 +1545,21 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         }
         // a chunk without super-steps issued no load for the next one
         pre = chain && cur.nsuper > 0;
-        flush(cur, ib);
+        // the ragged rest: whole vectors of every lane, then single elements
+        const uint32_t v0 = cur.nsuper * U, nv = cur.len / (kBlock * VEC) - v0;
+        if (nv != 0) {
+            const __amdgpu_buffer_rsrc_t grs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)cur.gbase, (short)0, (int)(cur.len * ESZG), kBufFlags);
+            const __amdgpu_buffer_rsrc_t trs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)cur.tbase, (short)0, (int)(cur.len * ESZT), kBufFlags);
+#pragma unroll 1
+            for (uint32_t u = 0; u < nv; ++u)
+                work(buf_load<BG, kLoadNT>(grs, (int)lane_off_g, (int)((v0 + u) * (kBlock * BG))),
+                     buf_load<BT, kLoadNT>(trs, (int)lane_off_t, (int)((v0 + u) * (kBlock * BT))), v0 + u, ib);
+            L.s_ulp += L.s_ulp32;
+            L.s_ulp32 = 0;
+        }
+        rest(cur, ib, (v0 + nv) * (kBlock * VEC), true);
         chunk_end(cur, ib, run_end);
         if (run_end) {
             run_end_reduce(cur, run_off);
@@ -1368,10 +1570,11 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
     }
 }
 
-// Three blocks per CU (12 waves) where the registers allow it without
-// spilling in the hot loop: f32 with two absolute thresholds, the common case.
+// Three blocks per CU (12 waves, 168 registers) where that spills nothing in
+// the hot loop: mixed pairs, and same-type pairs with up to four tolerances
+// (with eight, the wave's mismatch counts leave 172 to 190 registers).
 template <int DG, int DT, int NT, bool RT>
-constexpr int chunk_blocks_per_cu() { return (DG == DT && NT == 2 && !RT) ? 3 : 2; }
+constexpr int chunk_blocks_per_cu() { return (DG != DT || NT <= 4) ? 3 : 2; }
 
 // INJ: inject the test tensors' bit flips first (inj[pair], same decisions
 // as the injection kernel) and sign the flipped tensors; the chunk records

@@ -1,0 +1,10 @@
+// Pass 1 of the error signature for f16 pairs.
+#include "sig_chunk.h"
+
+namespace peat {
+
+hipError_t launch_sig_f16(const SigParams &p, int64_t n, const InjDesc *inj, hipStream_t s) {
+    return inj ? launch_kind_inject<PEAT_F16>(p, n, inj, s) : launch_kind<PEAT_F16, PEAT_F16>(p, n, s);
+}
+
+}  // namespace peat

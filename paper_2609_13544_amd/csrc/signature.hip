@@ -1,5 +1,6 @@
-// Error-signature kernels for gfx950: instantiation of pass 1 for same-type
-// pairs, pass 2 (sig_finalize) and the launchers.
+// Error-signature kernels for gfx950: pass 2 (sig_finalize) and the launchers
+// of both passes.  Pass 1 is instantiated in sig_f32.hip, sig_f16.hip,
+// sig_bf16.hip (same-type pairs), mixed.hip and mixed_f64.hip.
 #include "sig_chunk.h"
 
 namespace peat {
@@ -363,10 +364,11 @@ hipError_t launch_sig_chunks(const SigParams &p, const int64_t range[kKinds + 1]
         q.launch_elems = p.kind_elems[kind];
         hipError_t e;
         switch (kind) {
-            case 0: e = launch_kind<PEAT_F32, PEAT_F32>(q, n, s); break;
-            case 1: e = launch_kind<PEAT_F16, PEAT_F16>(q, n, s); break;
-            case 2: e = launch_kind<PEAT_BF16, PEAT_BF16>(q, n, s); break;
-            default: e = launch_sig_mixed_kind(q, kind, n, s); break;
+            case 0: e = launch_sig_f32(q, n, nullptr, s); break;
+            case 1: e = launch_sig_f16(q, n, nullptr, s); break;
+            case 2: e = launch_sig_bf16(q, n, nullptr, s); break;
+            case 3: case 8: case 9: e = launch_sig_mixed_f64(q, kind, n, s); break;
+            default: e = launch_sig_mixed(q, kind, n, s); break;
         }
         if (e != hipSuccess) return e;
     }
@@ -383,9 +385,9 @@ hipError_t launch_sig_chunks_inject(const SigParams &p, const int64_t range[kKin
         q.launch_elems = p.kind_elems[kind];
         hipError_t e;
         switch (kind) {
-            case 0: e = launch_kind_inject<PEAT_F32>(q, n, inj, s); break;
-            case 1: e = launch_kind_inject<PEAT_F16>(q, n, inj, s); break;
-            default: e = launch_kind_inject<PEAT_BF16>(q, n, inj, s); break;
+            case 0: e = launch_sig_f32(q, n, inj, s); break;
+            case 1: e = launch_sig_f16(q, n, inj, s); break;
+            default: e = launch_sig_bf16(q, n, inj, s); break;
         }
         if (e != hipSuccess) return e;
     }

@@ -119,8 +119,7 @@ __device__ __forceinline__ bool error_of(BG gb, BT tb, uint64_t &key, double &a)
 
 // Calls f(key, a) for every valid pair of chunk `cin` of pair d, each lane in
 // a fixed order: lane vectors (16 bytes of the wider side, four per step in
-// flight), then the ragged tail (or the whole chunk when a pointer is not
-// 16-byte aligned).
+// flight), then the ragged tail.  Buffer loads take any alignment.
 template <int DG, int DT, typename F>
 __device__ __forceinline__ void for_each_error(const SigDesc &d, int64_t cin, F &&f) {
     using PT = PairTr<DG, DT>;
@@ -133,7 +132,7 @@ __device__ __forceinline__ void for_each_error(const SigDesc &d, int64_t cin, F 
     const uint32_t len = (uint32_t)(rest < (int64_t(1) << d.chunk_log2) ? rest : (int64_t(1) << d.chunk_log2));
     const char *gbase = static_cast<const char *>(d.g) + off * ESZG;
     const char *tbase = static_cast<const char *>(d.t) + off * ESZT;
-    const uint32_t nvec = d.aligned ? len / VEC : 0;
+    const uint32_t nvec = len / VEC;
     if (nvec > 0) {
         const __amdgpu_buffer_rsrc_t grs =
             __builtin_amdgcn_make_buffer_rsrc((void *)gbase, (short)0, (int)(nvec * BG), kBufFlags);
@@ -191,7 +190,7 @@ __device__ __forceinline__ void for_each_error_vec(const SigDesc &d, int64_t cin
     const uint32_t len = (uint32_t)(rest < (int64_t(1) << d.chunk_log2) ? rest : (int64_t(1) << d.chunk_log2));
     const char *gbase = static_cast<const char *>(d.g) + off * ESZG;
     const char *tbase = static_cast<const char *>(d.t) + off * ESZT;
-    const uint32_t nvec = d.aligned ? len / VEC : 0;
+    const uint32_t nvec = len / VEC;
     constexpr int NB = VEC < 4 ? VEC : 4;                     // elements per call
     uint64_t key[NB];
     double a[NB];
