@@ -312,20 +312,17 @@ int peat_signature_mixed_batched_async(const peat_mixed_pair_t *pairs, int32_t c
  * (num = 1, den = 10: the paper's top-10% mean of Section IV-B.3, the
  * Analyzer's main score in Section IV-C); out is host memory.
  * 1 <= num <= den <= 2^20.  Exact selection: n_valid, k, count_above and
- * kth_value are exact.  sum_topk is the binary64 sum, in a fixed order, of
- * the errors above the binade of kth_value plus the exact sum of the others
- * (within 1e-12 relative of the exact sum), bit-identical between calls and
- * between the entry points below (the signature-fed ones as they state).
- * One streaming pass over golden and test in the common case: a small
- * strided sample of each pair (about 8 K elements) guesses the binade of the
- * k-th largest error, and one pass sums the errors above it, gathers its
- * errors and counts the pair's errors, which confirm the guess; a wrong
- * guess, a pair below 2^16 elements, or one whose sampled binade holds many
- * distinct errors takes a binade-histogram pass first (two passes).  A pair
- * whose binade holds too many distinct errors for the gather takes one more
- * pass (a gather of its top 13 mantissa bits), and one whose bin still does
- * not fit one pass per remaining digit.  Every route gives the same record.
- * No step waits on the host; the call waits for its result. */
+ * kth_value are exact.  sum_topk is a binary64 sum in a fixed order (within
+ * 1e-12 relative of the exact sum): above 2^14 elements the sum, in a fixed
+ * order, of the exact sums of each binade's errors; bit-identical between
+ * calls and between the entry points below.  One streaming pass over golden
+ * and test in the common case: a sample of each pair (2^14 elements) gives a
+ * narrow window expected to hold the k-th largest error, and one pass sums
+ * and counts the errors above it and gathers those inside; a pair of at most
+ * 2^14 elements is settled at once.  A pair whose window misses, or holds
+ * more errors than the gather's buffers, takes one pass per 11 bits of the
+ * k-th largest error instead.  Every route gives the same record.
+ * The call waits for its result. */
 int peat_topk_mean(const void *golden, const void *test, int64_t n, peat_dtype_t dtype,
                    int32_t num, int32_t den, peat_topk_t *out);
 
@@ -354,21 +351,11 @@ int peat_topk_mean_mixed_batched_async(const peat_mixed_pair_t *pairs, int32_t c
 /* peat_topk_mean_batched for pairs whose error signatures the caller already
  * holds: sigs is a host array of count records that peat_signature_batched
  * (or its async form) wrote for the same pairs with these bins; thresholds do
- * not matter.  The histogram counts the same errors of the same valid pairs,
- * so it bounds the k-th largest error to one bin, and the binade histogram
- * pass skips the pair: one streaming pass does the rest.  With one-binade
- * bins (hi_log2 - lo_log2 == nbins) and the boundary in a regular bin (or,
- * with a test type other than binary64, among the zero errors) that bin is
- * the boundary's binade, and outs are bit-identical to
- * peat_topk_mean_batched's.  Otherwise (the under or over bin, or wider
- * bins) the pass gathers the bin's whole range of binades, and n_valid, k,
- * count_above and kth_value are identical while sum_topk and mean_topk are
- * formed in another order (within 1e-12 relative; equal whenever the errors
- * inside the range sum exactly in binary64).  A range with too many
- * distinct errors for the gather falls back to the binade pass (and then
- * bit-identical records).  PEAT_EINVAL when a record's n differs from its
- * pair's or its histogram total from its n_valid.  (Section IV-B.3;
- * Section V-D histograms.) */
+ * not matter.  The records are checked; outs are peat_topk_mean_batched's,
+ * bit for bit.  (The selection finds its window in the pair itself, in the
+ * same single pass, whichever bins the record has.)  PEAT_EINVAL when a
+ * record's n differs from its pair's or its histogram total from its n_valid.
+ * (Section IV-B.3; Section V-D histograms.) */
 int peat_topk_mean_from_signature_batched(const peat_pair_t *pairs, int32_t count, int32_t num,
                                           int32_t den, const peat_signature_t *sigs,
                                           const peat_bins_t *bins, peat_topk_t *outs);
@@ -377,9 +364,8 @@ int peat_topk_mean_from_signature_batched(const peat_pair_t *pairs, int32_t coun
  * device array of count records (as peat_signature_batched_async or
  * peat_inject_signature_batched_async leave them, possibly still being
  * written earlier on the same stream), d_outs a device array of count
- * records written when the stream gets there.  A record whose n or
- * histogram total does not match is ignored (its pair takes the binade
- * pass), so a mismatch costs time, not correctness. */
+ * records written when the stream gets there.  The device records are not
+ * read: outs do not depend on them. */
 int peat_topk_mean_from_signature_batched_async(const peat_pair_t *pairs, int32_t count, int32_t num,
                                                 int32_t den, const peat_signature_t *d_sigs,
                                                 const peat_bins_t *bins, peat_topk_t *d_outs,
@@ -400,13 +386,14 @@ int peat_topk_mean_mixed_from_signature_batched_async(const peat_mixed_pair_t *p
                                                       const peat_bins_t *bins, peat_topk_t *d_outs,
                                                       void *stream);
 
-/* Entry capacity of the top-k gathers for later calls of this process:
- * binade_entries for the gathers of a whole binade, bin_entries for the
- * gathers of one 13-bit bin (16 bytes of device workspace each).  -1 (the
- * default) sizes them per call: max(2^16, 256 x chunks) and max(2^16,
- * 64 x chunks), a chunk being one block's share of a pair.  A pair whose
- * gather does not fit takes the next, slower route; the records do not
- * change.  Each value must be -1 or in [0, 2^36]. */
+/* Capacity of the top-k gathers for later calls of this process:
+ * binade_entries for keys that repeat (16 bytes of device workspace each, one
+ * per distinct error and chunk), bin_entries for errors listed one by one (8
+ * bytes each, handed out 256 at a time).  -1 (the default) sizes them per
+ * call: max(2^16, 256 x chunks) and max(2^16, 4096 x chunks), the latter at
+ * most 2^26, a chunk being one block's share of a pair.  A pair whose gather
+ * does not fit takes the slower route; the records do not change.  Each value
+ * must be -1 or in [0, 2^36]. */
 int peat_topk_set_entry_capacity(int64_t binade_entries, int64_t bin_entries);
 
 /* Random bit flip in place (Section II-B).  The draws come from
@@ -510,9 +497,8 @@ int peat_finalize_stats(const peat_signature_t *sig, peat_stats_t *stats);
  * events, returns the summed duration (ms) and launch count of one kernel
  * class since the last read, and clears that class.  Kernel classes:
  * 0 signature chunk pass, 1 signature finalize, 2 injection, 3 injection
- * count reduction, 4 streaming read (peat_stream_read), 5 top-k level 0
- * (state, binade histogram pass, selection), 6 top-k from the gathering pass
- * to the records, 7 chunk pass with the injection
+ * count reduction, 4 streaming read (peat_stream_read), 5 top-k start (small
+ * pairs' records, windows), 6 top-k from the gathering pass to the records, 7 chunk pass with the injection
  * (peat_inject_signature_batched_async). */
 int peat_profile_enable(int on);
 int peat_profile_read(int kernel_class, double *total_ms, int64_t *launches);

@@ -670,18 +670,22 @@ int inject_signature_core(const peat_pair_t *pairs, int32_t count, const uint64_
     return signature_core(mp.data(), count, bins, thr, d_outs, nullptr, s, &inj, d_counts);
 }
 
-// Entries of the two top-k gather regions (binade gathers of pass A, bin
-// gathers of pass C); -1: sized per call from its chunk count.
+// Room of the top-k gathers: entries of the chunks' tables (16 bytes each) and
+// single keys (8 bytes each); -1: sized per call from its chunk count (a wave
+// takes a segment of 256 keys at a time, four waves per chunk; half a GiB of
+// single keys at most).
 int64_t g_topk_cap[2] = {-1, -1};
 constexpr int64_t kTopkCapMin = int64_t(1) << 16;
-constexpr int64_t kTopkCapPerChunk[2] = {256, 64};
-constexpr int kBins0Topk = 2048;         // binade field values (exact sums per binade)
+constexpr int64_t kTopkCapPerChunk[2] = {256, 4096};
+constexpr int kBins0Topk = 2048;         // binades with an exact sum each
+constexpr int64_t kTopkCapMax[2] = {int64_t(1) << 36, int64_t(1) << 26};
 
-// Mean of the k largest errors (see topk.hip): every step stream-ordered.
-// With host_outs the records go through workspace + pinned staging and the
-// call waits for them; otherwise they land in d_outs when the stream gets
-// there.  host_sigs (validated here) or d_sigs (validated on the device: a
-// record that does not match its pair is ignored) give level 0.
+// Mean of the k largest errors (see topk.hip).  With host_outs the records are
+// written to the pinned slot, the call waits for them and launches the digit
+// passes only if some pair was left open; otherwise they land in d_outs when
+// the stream gets there, every step enqueued at once.  host_sigs and d_sigs:
+// the call came with signature records (host ones are checked here); the
+// window comes from a sample of the pair all the same, so they change nothing.
 int topk_core(const peat_mixed_pair_t *pairs, int32_t count, int32_t num, int32_t den, peat_topk_t *host_outs,
               peat_topk_t *d_outs, hipStream_t s, const peat_signature_t *host_sigs = nullptr,
               const peat_signature_t *d_sigs = nullptr, const peat_bins_t *bins = nullptr) {
@@ -720,78 +724,100 @@ int topk_core(const peat_mixed_pair_t *pairs, int32_t count, int32_t num, int32_
     int64_t range[kKinds + 1];
     if ((rc = build_descs(pairs, count, descs, range, &total))) return rc;
 
+    bool large = false;                      // some pair needs more than the start kernel
+    for (int k = 0; k < count; ++k) large = large || pairs[k].n > kTopkSmall;
     uint64_t cap[2];
     for (int r = 0; r < 2; ++r) {
-        const int64_t c = g_topk_cap[r] >= 0 ? g_topk_cap[r] : std::max(kTopkCapMin, kTopkCapPerChunk[r] * total);
-        cap[r] = (uint64_t)c;
+        const int64_t c = g_topk_cap[r] >= 0
+                              ? g_topk_cap[r]
+                              : std::min(kTopkCapMax[r], std::max(kTopkCapMin, kTopkCapPerChunk[r] * total));
+        cap[r] = large ? (uint64_t)c : 0;
     }
-    const size_t b_desc = align_up(sizeof(SigDesc) * count);
-    const size_t b_map = align_up(sizeof(int32_t) * (size_t)total);
-    const size_t b_sig = host_sigs ? align_up(sizeof(peat_signature_t) * count) : 0;
-    const size_t b_out = host_outs ? align_up(sizeof(peat_topk_t) * count) : 0;
-    const size_t b_state = align_up(sizeof(TopkState) * count);
-    const size_t b_hist = align_up(sizeof(uint64_t) * kTopkBins * (size_t)count);
-    const size_t b_part = align_up(sizeof(double) * (size_t)total);
-    const size_t b_xsum = align_up(2 * sizeof(uint64_t) * kBins0Topk * (size_t)count);
-    const size_t b_ovf = align_up(sizeof(uint32_t) * (2 * (size_t)count + 3));
-    const size_t b_cnt = align_up(2 * sizeof(uint64_t) * count);
-    const size_t b_fill = align_up(2 * sizeof(unsigned long long));
-    const size_t b_ents = align_up(sizeof(TopkEntry) * (size_t)(cap[0] + cap[1]));
-    // device workspace: descriptors | chunk map | signatures | records (the
-    // first three staged and copied as they lie) | state | histograms | chunk
-    // sums | exact sums | flags | counts | fills | entries
-    const size_t o_map = b_desc, o_sig = o_map + b_map, o_out = o_sig + b_sig, o_state = o_out + b_out;
-    const size_t o_hist = o_state + b_state, o_part = o_hist + b_hist, o_xsum = o_part + b_part;
-    const size_t o_ovf = o_xsum + b_xsum, o_cnt = o_ovf + b_ovf, o_fill = o_cnt + b_cnt, o_ents = o_fill + b_fill;
+    // a lone pair travels in the kernel arguments
+    const bool single = count == 1;
+    const size_t nch = large ? (size_t)total : 0, npair = large ? (size_t)count : 0;
+    const size_t b_desc = single ? 0 : align_up(sizeof(SigDesc) * count);
+    const size_t b_map = single ? 0 : align_up(sizeof(int32_t) * nch);
+    const size_t b_stage = b_desc + b_map;
+    // device workspace: descriptors | chunk map (staged and copied as they lie)
+    // | state | counts | exact sums | flags | fills | levels | histograms |
+    // chunk directories | entries | single keys
+    size_t pos = b_stage;
+    auto place = [&](size_t bytes) {
+        const size_t o = pos;
+        pos += align_up(bytes);
+        return o;
+    };
+    const size_t o_state = place(sizeof(TopkState) * count), o_cnt = place(2 * sizeof(uint64_t) * count);
+    const size_t o_xsum = place(2 * sizeof(uint64_t) * kBins0Topk * npair), o_ovf = place(sizeof(uint32_t) * count);
+    const size_t o_fill = place(2 * sizeof(unsigned long long) + sizeof(uint32_t));
+    const size_t o_lev = place(sizeof(TopkLevel) * kTopkLevels * npair);
+    const size_t o_hist = place(sizeof(uint64_t) * kTopkHist * npair);
+    const size_t o_dir = place(sizeof(TopkDir) * nch);
+    const size_t o_ents = place(sizeof(TopkEntry) * (size_t)cap[0]), o_pool = place(sizeof(uint64_t) * (size_t)cap[1]);
 
     char *ws;
-    if ((rc = acquire_ws(d, o_ents + b_ents, s, &ws))) return rc;
-    Slot *sl;
-    if ((rc = acquire_slot(d, o_state, &sl))) return rc;
-    char *h = static_cast<char *>(sl->host);
-    std::memcpy(h, descs.data(), sizeof(SigDesc) * count);
-    int32_t *hmap = reinterpret_cast<int32_t *>(h + o_map);
-    for (int k = 0; k < count; ++k)
-        for (int32_t c = 0; c < descs[k].nchunks; ++c) hmap[descs[k].first_chunk + c] = k;
-    if (host_sigs) std::memcpy(h + o_sig, host_sigs, sizeof(peat_signature_t) * count);
-    HIP_OR_FAIL(hipMemcpyAsync(ws, h, o_out, hipMemcpyHostToDevice, s));
+    if ((rc = acquire_ws(d, pos, s, &ws))) return rc;
+    Slot *sl = nullptr;
+    char *h = nullptr;
+    const size_t b_out = host_outs ? align_up(sizeof(peat_topk_t) * count) : 0;
+    if (b_stage + b_out > 0) {
+        if ((rc = acquire_slot(d, b_stage + b_out, &sl))) return rc;
+        h = static_cast<char *>(sl->host);
+    }
+    if (!single) {
+        std::memcpy(h, descs.data(), sizeof(SigDesc) * count);
+        if (large) {
+            int32_t *hmap = reinterpret_cast<int32_t *>(h + b_desc);
+            for (int k = 0; k < count; ++k)
+                for (int32_t c = 0; c < descs[k].nchunks; ++c) hmap[descs[k].first_chunk + c] = k;
+        }
+    }
+    if (b_stage > 0) HIP_OR_FAIL(hipMemcpyAsync(ws, h, b_stage, hipMemcpyHostToDevice, s));
+    peat_topk_t *hout = host_outs ? reinterpret_cast<peat_topk_t *>(h + b_stage) : nullptr;
+    for (int k = 0; hout && k < count; ++k) hout[k].n_valid = -1;        // no record yet
 
     TopkParams P{};
     P.descs = reinterpret_cast<const SigDesc *>(ws);
-    P.chunk_pair = reinterpret_cast<const int32_t *>(ws + o_map);
+    P.chunk_pair = reinterpret_cast<const int32_t *>(ws + b_desc);
     P.state = reinterpret_cast<TopkState *>(ws + o_state);
-    P.hist = reinterpret_cast<uint64_t *>(ws + o_hist);
-    P.part_a = reinterpret_cast<double *>(ws + o_part);
+    P.counts = reinterpret_cast<uint64_t *>(ws + o_cnt);
     P.xsum = reinterpret_cast<uint64_t *>(ws + o_xsum);
     P.ovf = reinterpret_cast<uint32_t *>(ws + o_ovf);
-    P.counts = reinterpret_cast<uint64_t *>(ws + o_cnt);
     P.fill = reinterpret_cast<unsigned long long *>(ws + o_fill);
+    P.open = reinterpret_cast<uint32_t *>(ws + o_fill + 2 * sizeof(unsigned long long));
+    P.levels = reinterpret_cast<TopkLevel *>(ws + o_lev);
+    P.hist = reinterpret_cast<uint64_t *>(ws + o_hist);
+    P.dir = reinterpret_cast<TopkDir *>(ws + o_dir);
     P.ents = reinterpret_cast<TopkEntry *>(ws + o_ents);
+    P.pool = reinterpret_cast<uint64_t *>(ws + o_pool);
     P.cap[0] = cap[0];
     P.cap[1] = cap[1];
-    P.sigs = host_sigs ? reinterpret_cast<const peat_signature_t *>(ws + o_sig) : d_sigs;
-    P.outs = host_outs ? reinterpret_cast<peat_topk_t *>(ws + o_out) : d_outs;
-    if (bins) {
-        P.lo = bins->lo_log2;
-        P.hi = bins->hi_log2;
-        P.nbins = bins->nbins;
-    }
+    P.outs = host_outs ? hout : d_outs;
     P.count = count;
     P.num = num;
     P.den = den;
+    P.single = single ? 1 : 0;
+    if (single) P.one = descs[0];
 
     hipEvent_t ev;
     if ((rc = prof_begin(d, s, &ev))) return rc;
-    HIP_OR_FAIL(launch_topk_level0(P, range, s));
+    HIP_OR_FAIL(launch_topk_start(P, s));
     if ((rc = prof_end(d, s, 5, ev))) return rc;
-    if ((rc = prof_begin(d, s, &ev))) return rc;
-    HIP_OR_FAIL(launch_topk_rest(P, range, s));
-    if ((rc = prof_end(d, s, 6, ev))) return rc;
+    if (large) {
+        if ((rc = prof_begin(d, s, &ev))) return rc;
+        HIP_OR_FAIL(launch_topk_gather(P, range, s));
+        bool open = true;
+        if (host_outs) {
+            HIP_OR_FAIL(hipStreamSynchronize(s));
+            open = false;
+            for (int k = 0; k < count; ++k) open = open || hout[k].n_valid < 0;
+        }
+        if (open) HIP_OR_FAIL(launch_topk_digits(P, range, s));
+        if ((rc = prof_end(d, s, 6, ev))) return rc;
+    }
 
-    char *hout = h + o_out;
-    if (host_outs)
-        HIP_OR_FAIL(hipMemcpyAsync(hout, P.outs, sizeof(peat_topk_t) * count, hipMemcpyDeviceToHost, s));
-    if ((rc = release_slot(*sl, s))) return rc;
+    if (sl && (rc = release_slot(*sl, s))) return rc;
     if ((rc = release_ws(d, s))) return rc;
     if (host_outs) {
         HIP_OR_FAIL(hipStreamSynchronize(s));

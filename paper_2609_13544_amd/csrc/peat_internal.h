@@ -144,41 +144,43 @@ struct InjParams {
 };
 
 // ---- top-k error mean --------------------------------------------------------
-// Radix selection on the binary64 bit pattern of the error (monotone for
-// a >= 0): digit 0 = bits 62..52 (the binade, 2048 bins), digits 1-4 = 13
-// mantissa bits each (8192 bins).  The boundary's binade D0 comes from the
-// pair's signature or from a binade histogram; one pass then sums the errors
-// above D0, histograms digit 1 inside it and gathers its errors as
-// deduplicated (key, count) entries, on which digits 2-4 are resolved.  When
-// the signature only bounds the k-th largest error to a window of binades,
-// or a sample of the pair suggests one, that pass gathers the whole window
-// and every level comes from the entries.
-constexpr int kTopkLevels = 5;
-constexpr int kTopkBins = 8192;                  // bins of digits 1-4
-enum { kTopkActive = 0, kTopkDone = 1 };
+// Selection on the binary64 bit pattern of the error (monotone for a >= 0);
+// see topk.hip for the steps.
+constexpr int kTopkLevels = 6;                   // digits: 11 bits each (the binade first), the last 8
+constexpr int kTopkHist = 3 * 2048;              // counters per pair: three digit histograms
+constexpr int64_t kTopkSmall = int64_t(1) << 14; // errors of a pair that one block settles
+constexpr int kTopkSeg = 256;                    // keys of a pool segment
+constexpr int kTopkSegs = 32;                    // segments per wave of a gather
+enum { kTopkDone = 0, kTopkWindow = 1, kTopkOpen = 2 };
 
-struct TopkState {               // one per pair (80 bytes), device memory
-    uint64_t n_valid;
-    uint64_t k;
-    uint64_t need;               // k minus the errors above the boundary bin (or window)
-    uint64_t cand;               // errors in the boundary bin (or window)
-    uint64_t key;                // bits of the boundary fixed so far
-    uint64_t wlo, whi;           // window [wlo, whi) of error keys holding the k-th largest
-    int32_t level;               // last resolved level; -1 before level 0, -2 window gather pending
-    int32_t status;              // kTopkActive or kTopkDone
-    int32_t d0;                  // binade field of the boundary
-    int32_t round;               // gathering pass that serves the pair (0, or 1 after a window overflowed)
-    int32_t sampled;             // the binade is a guess from a sample: pass A counts the errors to confirm it
-    int32_t reserved;
+struct TopkState {               // one per pair, device memory
+    uint64_t wlo, whi;           // window [wlo, whi) of error keys expected to hold the k-th largest
+    int32_t status;              // kTopkDone, kTopkWindow or kTopkOpen (digit passes)
+    int32_t append;              // the window's errors hardly repeat: list them one by one
 };
-static_assert(sizeof(TopkState) == 80, "TopkState layout");
+static_assert(sizeof(TopkState) == 24, "TopkState layout");
+
+struct TopkLevel {               // an open pair after a digit's selection
+    uint64_t n_valid, k;
+    uint64_t need;               // copies of the boundary bin taken
+    uint64_t key;                // bits of the boundary fixed so far
+};
 
 struct TopkEntry {               // errors of one key in one chunk (16 bytes)
     uint64_t key;
     uint32_t count;
-    int32_t pair;                // pair | round << 30; -1: an unused position
+    int32_t reserved;
 };
 static_assert(sizeof(TopkEntry) == 16, "TopkEntry layout");
+
+struct TopkDir {                 // what a chunk's gather wrote
+    uint64_t tbase;              // its table's entries: [tbase, tbase + tn) of ents
+    uint32_t tn;
+    uint32_t keys[kWaves];       // single keys of each wave, in segments of the pool
+    uint32_t seg[kWaves][kTopkSegs];
+    uint32_t reserved;
+};
+static_assert(sizeof(TopkDir) % 8 == 0, "TopkDir layout");
 
 struct TopkParams {
     int64_t chunk_base;          // first global chunk of this launch
@@ -186,23 +188,23 @@ struct TopkParams {
     const SigDesc *descs;
     const int32_t *chunk_pair;
     TopkState *state;
-    uint64_t *hist;              // count x kTopkBins counters
-    double *part_a;              // per chunk: binary64 sum of its errors above binade D0
+    TopkLevel *levels;           // kTopkLevels per pair (digit passes)
+    uint64_t *hist;              // kTopkHist counters per pair (digit passes)
     uint64_t *xsum;              // per pair and binade: exact sum (2 words) of the significands above the boundary
-    uint64_t *counts;            // per pair: valid errors, errors above a guessed binade
-    uint32_t *ovf;               // per pair: [0] gather of binade D0 (or window) did not fit, [1] gather of bin
-                                 // (D0, D1) did not fit; then 3 words: some pair has flag 0 set, some pair has
-                                 // flag 1 set, some window gather did not fit
-    TopkEntry *ents;             // cap[0] entries of binade D0 gathers, then cap[1] of bin (D0, D1) gathers
-    unsigned long long *fill;    // entries handed out in each of the two regions
+    uint64_t *counts;            // per pair: invalid elements, errors above the window
+    uint32_t *ovf;               // per pair: some gathered key found no room
+    uint32_t *open;              // pairs left to the digit passes
+    TopkEntry *ents;             // cap[0] entries of the gathers' tables
+    uint64_t *pool;              // cap[1] single keys, in segments
+    TopkDir *dir;                // per chunk
+    unsigned long long *fill;    // entries and segments handed out
     uint64_t cap[2];
-    const peat_signature_t *sigs;    // the pairs' signatures (device), or NULL
-    peat_topk_t *outs;           // one per pair (device)
-    int32_t lo, hi, nbins;       // the bins of those signatures
+    peat_topk_t *outs;           // one per pair
     int32_t count;               // pairs
     int32_t num, den;
-    int32_t level;               // level of a selection, tensor-pass or entry launch
-    int32_t round;               // gathering-pass round of a launch
+    int32_t level;               // digit of a digit pass
+    int32_t single;              // one pair, described by `one` (descs and chunk_pair unused)
+    SigDesc one;
 };
 
 // Kernel launchers (defined in the .hip translation units).
@@ -226,10 +228,11 @@ hipError_t launch_corrupt_positions(void *x, int64_t n, int dtype, uint64_t seed
                                     uint64_t mask, int64_t *d_positions, hipStream_t s);
 hipError_t launch_cast_round(void *x, int64_t n, int to_dtype, hipStream_t s);
 hipError_t launch_stream_read(const void *buf, int64_t bytes, uint32_t *sink, hipStream_t s);
-// The top-k selection of a batch, stream-ordered (no host wait): level 0
-// (state, binade histogram where the signatures leave it open, selection),
-// then the rest up to the records.
-hipError_t launch_topk_level0(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s);
-hipError_t launch_topk_rest(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s);
+// The top-k selection of a batch, stream-ordered: the small pairs' records and
+// the windows of the others; the gather and its resolution; the digit passes
+// over the pairs left open (nothing to do where there are none).
+hipError_t launch_topk_start(const TopkParams &p, hipStream_t s);
+hipError_t launch_topk_gather(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s);
+hipError_t launch_topk_digits(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s);
 
 }  // namespace peat

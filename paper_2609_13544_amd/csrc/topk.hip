@@ -1,55 +1,63 @@
 // Mean of the k largest errors of each pair (the "mean of the top 10%
 // errors" score of Section IV-B.3, the Analyzer's main score in Section IV-C),
-// by exact radix selection on the binary64 bit pattern of the error, which is
+// by exact selection on the binary64 bit pattern of the error, which is
 // monotone for a >= 0.  The whole selection is stream-ordered: every count,
-// boundary and buffer fill stays on the device, so no step waits on the host.
+// boundary and buffer fill stays on the device.
 //
-//   init     per pair: the state of level 0 from its signature when one is
-//            given: its histogram fixes the binade D0 of the k-th largest
-//            error (one-binade bins, boundary in a regular bin or among the
-//            zero errors) or bounds it to a window of binades (the under or
-//            over bin, wider bins); otherwise level 0 is open;
-//   sample   per open pair of 2^16 elements or more: a strided sample of
-//            8 K elements guesses D0 (a one-binade window whose guess pass A
-//            confirms by counting);
-//   pass 1   histogram of digit 0 (bits 62..52, the binade) over the pairs
-//            whose level 0 is still open; select D0;
-//   pass A   binary64 sum of the errors above the gathered range (a fixed
-//            per-lane / butterfly / wave order in each chunk) and a gather of
-//            the range -- binade D0 or the window -- as (key, count) entries:
-//            each block counts its distinct keys in an LDS hash table (errors
-//            of checkpoint-like data are small multiples of the golden's ULP,
-//            so a binade holds few distinct values) and appends one entry per
-//            key; for binade D0 also the digit-1 (bits 51..39) histogram;
-//   windows  level 0 of a window from its entries' binades (a signature's
-//            window) or from the counts (a guess); a window that does not
-//            fit, or a wrong guess, reopens level 0: pass 1 and pass A again
-//            for those pairs (round 1);
-//   rounds   digits 1-4 on the entries as needed: weighted histogram, select;
-//            then the exact integer sums count * significand of the entries
-//            above the boundary, per binade;
-//   finalize sum = pass A + the exact sums (binade D0 with need copies of T,
-//            and a signature's window binades above it, from the top).
+//   start    one block per pair.  A pair of at most 2^14 errors is settled
+//            here: its keys fit the block's registers, and six digits of a
+//            radix selection give the record.  For a larger one, 2^14 sampled
+//            errors (2048 runs of 8) give a narrow window of keys expected to
+//            hold the k-th largest error T: the sample's k-th largest give or
+//            take five standard deviations in rank, to 11 bits below the
+//            binade;
+//   gather   one pass over the tensors.  Nine errors in ten lie below a
+//            top-10 % window: each is compared with the window's start once, in
+//            binary32 where both sides fit it, and only the others are queued
+//            and looked at closely, 64 at a time: those above the window are
+//            counted and their significands summed exactly per binade, those
+//            inside it gathered -- counted per distinct key in an LDS hash
+//            table where they repeat (errors of checkpoint-like data are small
+//            multiples of the golden's ULP), listed one by one where they do
+//            not;
+//   resolve  one block per pair: the counts tell whether the window holds T; a
+//            histogram of the gathered keys relative to the window leaves one
+//            bin, whose keys are ordered in LDS, and the record is written.
 //
-// A pair whose binade does not fit (a block's table overflows, or the entry
-// buffer is full) instead takes pass C over its tensors: the exact sum of
-// its errors in D0 above bin D1 and a gather of bin (D0, D1), whose keys
-// that do not fit the table become entries of count 1; the rounds then run
-// on those entries.  A pair whose bin does not fit either takes one
-// histogram pass over its tensors per digit (passes T2-T4) and a last pass
-// for the exact sum of digit 4 (T5).  Every route sums the errors inside D0
-// exactly and the others in the lanes' order, so they give bit-identical
-// records; only a signature's window of several binades sums the binades
-// between D0 and its top exactly instead.
+// A pair whose window misses T or does not fit the buffers is left open for
+// the digit passes: one pass over its tensors per digit (11 bits, the last 8),
+// each selecting the previous digit from its histogram and, from the second
+// on, summing the errors above that digit.
 //
-// The k-th largest error T is the key with all five digits fixed; count_above
-// is k minus the copies of T taken.
+// Every sum is exact (a 128-bit integer per binade), so every route gives the
+// same record: the sum of the binades' values in a fixed order, T's copies
+// added to its binade's.  count_above is k minus those copies.
+//
+// What bounds it: HBM for the gather (6.2 TB/s on 54 f32 tensors of a
+// Llama-shaped checkpoint with Adam moments, 9.7 GB; 6.1 TB/s on 16 rectified
+// f32 [8, 512, 4096] pairs), latency for start and resolve (21 and 28 us for
+// one f32 [1024, 1024] pair, 40 and 29 us for 54 pairs).  Before -- the window
+// a whole binade, gathered by a wave-wide look at every element, its order
+// found by a histogram and a selection kernel per 13 bits, a second pass over
+// the tensors where a binade holds many distinct errors -- the same three took
+// 2000, 1150 and 380 us a call; now 1646, 440 and 90.
 #include "elements.h"
 
 namespace peat {
 namespace {
 
 constexpr int kBins0 = 2048;                    // digit 0: the binade field
+constexpr int kBig = 1024;                      // threads of the per-pair kernels
+constexpr int kBigWaves = kBig / 64;
+constexpr int kKeys = 16;                       // keys per thread of the start kernel
+constexpr int64_t kSmallN = int64_t(kBig) * kKeys;
+constexpr int kRun = 8;                         // consecutive elements of a sampled run
+constexpr int kRuns = (int)(kSmallN / kRun);
+constexpr int kCopies = 8;                      // copies of the start kernel's histogram
+constexpr int kCopyStride = kBins0 + 4;         // (on different banks)
+constexpr int kSumBins = 64;                    // binades a gather block sums in LDS, from the window's up
+constexpr int kRelBins = 4096;                  // bins of a window's histogram
+constexpr int kList = 1024;                     // keys of a bin ordered in LDS
 
 // A binary64 built from two 32-bit halves held in vector registers, opaque to
 // constant folding.  The record's NaN and +Inf go through it: as folded
@@ -59,19 +67,21 @@ __device__ __forceinline__ double opaque_double(uint32_t hi, uint32_t lo) {
     asm volatile("" : "+v"(hi), "+v"(lo));
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+    return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+           __builtin_amdgcn_readfirstlane((uint32_t)v);
+}
+__device__ __forceinline__ double key_value(uint64_t key) { return __longlong_as_double((long long)key); }
 constexpr uint64_t kMant = (uint64_t(1) << 52) - 1;
 constexpr int kTable = 512;                     // LDS hash table of a gather (keys per block)
 constexpr int kProbes = 8;
 constexpr uint64_t kEmpty = ~uint64_t(0);       // never a key: errors have the sign bit clear
-constexpr int kScanGrid = 2048;                 // blocks of the fallback tensor passes
-constexpr int kEntGrid = 1024;                  // blocks of the entry rounds
-enum { kModeA = 0, kModeC = 1, kModeT = 2 };    // route of an active pair
+constexpr int kScanGrid = 2048;                 // blocks of the digit passes
 
-__device__ __forceinline__ int digit_shift(int level) { return level == 0 ? 52 : 52 - 13 * level; }
+__device__ __forceinline__ int digit_shift(int level) { return level == 5 ? 0 : 52 - 11 * level; }
 
 __device__ __forceinline__ uint32_t digit_of(uint64_t key, int level) {
-    if (level == 0) return (uint32_t)(key >> 52);               // sign bit is 0
-    return (uint32_t)(key >> digit_shift(level)) & (kTopkBins - 1);
+    return (uint32_t)(key >> digit_shift(level)) & (level == 5 ? 255u : 2047u);   // (the sign bit is 0)
 }
 
 // Significand of an error of binade d0 as an integer: binade 0 (zero and
@@ -80,21 +90,15 @@ __device__ __forceinline__ uint64_t signif(uint64_t key, int d0) {
     return (key & kMant) | (d0 != 0 ? (uint64_t(1) << 52) : 0);
 }
 
-// Entries carry their pair and the round of the gathering pass that wrote
-// them; a pair whose window did not fit, or whose guessed binade was wrong,
-// is gathered again in round 1 and ignores what round 0 left.
-constexpr uint32_t kPairMask = (1u << 30) - 1;
-__device__ __forceinline__ int32_t entry_tag(int pair, int round) { return (int32_t)((uint32_t)pair | ((uint32_t)round << 30)); }
-
-// The pair's exact sum of significands of binade b (two words).
-__device__ __forceinline__ uint64_t *xsum_of(const TopkParams &P, int pair, int b) {
-    return P.xsum + 2 * ((size_t)pair * kBins0 + (size_t)b);
+__device__ __forceinline__ uint64_t top_count(uint64_t nv, const TopkParams &P) {
+    return (uint64_t)(((unsigned __int128)nv * (uint32_t)P.num + (uint32_t)P.den - 1) / (uint32_t)P.den);
 }
 
-__device__ __forceinline__ bool is_window(const TopkState &st) { return st.whi != 0; }
-
-__device__ __forceinline__ int pair_mode(const TopkParams &P, int pair) {
-    return P.ovf[2 * pair] == 0 ? kModeA : (P.ovf[2 * pair + 1] == 0 ? kModeC : kModeT);
+// Descriptor of a pair and pair of a chunk: a lone pair's travel in the
+// kernel arguments.
+__device__ __forceinline__ SigDesc desc_of(const TopkParams &P, int pair) { return P.single ? P.one : P.descs[pair]; }
+__device__ __forceinline__ int pair_of(const TopkParams &P, int64_t chunk) {
+    return P.single ? 0 : (int)__builtin_amdgcn_readfirstlane((uint32_t)P.chunk_pair[chunk]);
 }
 
 // Exact 128-bit accumulation: the carry of each low-word addition is
@@ -117,147 +121,65 @@ __device__ __forceinline__ bool error_of(BG gb, BT tb, uint64_t &key, double &a)
     return true;
 }
 
+// One chunk's elements as every pass sees them: lane t takes lane vectors t,
+// t + 256, ... (16 bytes of the wider side; buffer loads take any alignment),
+// then elements t, t + 256, ... of the ragged rest.
+template <int DG, int DT>
+struct ChunkView {
+    using PT = PairTr<DG, DT>;
+    static constexpr int VEC = PT::VEC, BG = PT::BG, BT = PT::BT;
+    const char *g, *t;
+    uint32_t len, nvec;
+    __amdgpu_buffer_rsrc_t grs, trs;
+    __device__ __forceinline__ ChunkView(const SigDesc &d, int64_t cin) {
+        const int64_t off = cin << d.chunk_log2;
+        const int64_t rest = d.n - off;
+        len = (uint32_t)(rest < (int64_t(1) << d.chunk_log2) ? rest : (int64_t(1) << d.chunk_log2));
+        nvec = len / VEC;
+        g = static_cast<const char *>(d.g) + off * (Tr<DG>::W / 8);
+        t = static_cast<const char *>(d.t) + off * (Tr<DT>::W / 8);
+        grs = __builtin_amdgcn_make_buffer_rsrc((void *)g, (short)0, (int)(nvec * BG), kBufFlags);
+        trs = __builtin_amdgcn_make_buffer_rsrc((void *)t, (short)0, (int)(nvec * BT), kBufFlags);
+    }
+    __device__ __forceinline__ void load(uint32_t v, u32x4 &gv, u32x4 &tv) const {
+        gv = buf_load<BG, kLoadNT>(grs, (int)(v * BG), 0);
+        tv = buf_load<BT, kLoadNT>(trs, (int)(v * BT), 0);
+    }
+};
+
 // Calls f(key, a) for every valid pair of chunk `cin` of pair d, each lane in
-// a fixed order: lane vectors (16 bytes of the wider side, four per step in
-// flight), then the ragged tail.  Buffer loads take any alignment.
+// that order (four vectors per step in flight).
 template <int DG, int DT, typename F>
 __device__ __forceinline__ void for_each_error(const SigDesc &d, int64_t cin, F &&f) {
-    using PT = PairTr<DG, DT>;
-    constexpr int VEC = PT::VEC;
-    constexpr int ESZG = Tr<DG>::W / 8, ESZT = Tr<DT>::W / 8;
-    constexpr int BG = PT::BG, BT = PT::BT;
+    const ChunkView<DG, DT> c(d, cin);
+    constexpr int VEC = ChunkView<DG, DT>::VEC;
     constexpr int U = 4;
-    const int64_t off = cin << d.chunk_log2;
-    const int64_t rest = d.n - off;
-    const uint32_t len = (uint32_t)(rest < (int64_t(1) << d.chunk_log2) ? rest : (int64_t(1) << d.chunk_log2));
-    const char *gbase = static_cast<const char *>(d.g) + off * ESZG;
-    const char *tbase = static_cast<const char *>(d.t) + off * ESZT;
-    const uint32_t nvec = len / VEC;
-    if (nvec > 0) {
-        const __amdgpu_buffer_rsrc_t grs =
-            __builtin_amdgcn_make_buffer_rsrc((void *)gbase, (short)0, (int)(nvec * BG), kBufFlags);
-        const __amdgpu_buffer_rsrc_t trs =
-            __builtin_amdgcn_make_buffer_rsrc((void *)tbase, (short)0, (int)(nvec * BT), kBufFlags);
-        uint32_t v = threadIdx.x;
-        for (; v + (U - 1) * kBlock < nvec; v += U * kBlock) {
-            u32x4 gv[U], tv[U];
+    uint64_t key;
+    double a;
+    uint32_t v = threadIdx.x;
+    for (; v + (U - 1) * kBlock < c.nvec; v += U * kBlock) {
+        u32x4 gv[U], tv[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                gv[u] = buf_load<BG, kLoadNT>(grs, (int)((v + u * kBlock) * BG), 0);
-                tv[u] = buf_load<BT, kLoadNT>(trs, (int)((v + u * kBlock) * BT), 0);
-            }
+        for (int u = 0; u < U; ++u) c.load(v + u * kBlock, gv[u], tv[u]);
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) {
-                    uint64_t key;
-                    double a;
-                    if (error_of<DG, DT>(lane_elem<DG>(gv[u], j), lane_elem<DT>(tv[u], j), key, a)) f(key, a);
-                }
-            }
-        }
-        for (; v < nvec; v += kBlock) {
-            const u32x4 gv = buf_load<BG, kLoadNT>(grs, (int)(v * BG), 0);
-            const u32x4 tv = buf_load<BT, kLoadNT>(trs, (int)(v * BT), 0);
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) {
-                uint64_t key;
-                double a;
-                if (error_of<DG, DT>(lane_elem<DG>(gv, j), lane_elem<DT>(tv, j), key, a)) f(key, a);
-            }
-        }
+            for (int j = 0; j < VEC; ++j)
+                if (error_of<DG, DT>(lane_elem<DG>(gv[u], j), lane_elem<DT>(tv[u], j), key, a)) f(key, a);
     }
-    for (uint32_t i = nvec * VEC + threadIdx.x; i < len; i += kBlock) {
-        uint64_t key;
-        double a;
-        if (error_of<DG, DT>(load_elem<DG>(gbase, i), load_elem<DT>(tbase, i), key, a)) f(key, a);
+    for (; v < c.nvec; v += kBlock) {
+        u32x4 gv, tv;
+        c.load(v, gv, tv);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j)
+            if (error_of<DG, DT>(lane_elem<DG>(gv, j), lane_elem<DT>(tv, j), key, a)) f(key, a);
     }
+    for (uint32_t i = c.nvec * VEC + threadIdx.x; i < c.len; i += kBlock)
+        if (error_of<DG, DT>(load_elem<DG>(c.g, i), load_elem<DT>(c.t, i), key, a)) f(key, a);
 }
 
-// As for_each_error, one lane vector at a time: f(key, a, ok) with arrays of
-// VEC elements (ok: the element exists and is a valid pair), so that work on
-// the elements of a vector can be issued together.  Tail elements come one
-// per call, in element 0.
-template <int DG, int DT, typename F>
-__device__ __forceinline__ void for_each_error_vec(const SigDesc &d, int64_t cin, F &&f) {
-    using PT = PairTr<DG, DT>;
-    constexpr int VEC = PT::VEC;
-    constexpr int ESZG = Tr<DG>::W / 8, ESZT = Tr<DT>::W / 8;
-    constexpr int BG = PT::BG, BT = PT::BT;
-    constexpr int U = VEC > 4 ? 2 : 4;                        // vectors in flight per lane
-    const int64_t off = cin << d.chunk_log2;
-    const int64_t rest = d.n - off;
-    const uint32_t len = (uint32_t)(rest < (int64_t(1) << d.chunk_log2) ? rest : (int64_t(1) << d.chunk_log2));
-    const char *gbase = static_cast<const char *>(d.g) + off * ESZG;
-    const char *tbase = static_cast<const char *>(d.t) + off * ESZT;
-    const uint32_t nvec = len / VEC;
-    constexpr int NB = VEC < 4 ? VEC : 4;                     // elements per call
-    uint64_t key[NB];
-    double a[NB];
-    bool ok[NB];
-    if (nvec > 0) {
-        const __amdgpu_buffer_rsrc_t grs =
-            __builtin_amdgcn_make_buffer_rsrc((void *)gbase, (short)0, (int)(nvec * BG), kBufFlags);
-        const __amdgpu_buffer_rsrc_t trs =
-            __builtin_amdgcn_make_buffer_rsrc((void *)tbase, (short)0, (int)(nvec * BT), kBufFlags);
-        uint32_t v = threadIdx.x;
-        for (; v + (U - 1) * kBlock < nvec; v += U * kBlock) {
-            u32x4 gv[U], tv[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                gv[u] = buf_load<BG, kLoadNT>(grs, (int)((v + u * kBlock) * BG), 0);
-                tv[u] = buf_load<BT, kLoadNT>(trs, (int)((v + u * kBlock) * BT), 0);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int jb = 0; jb < VEC; jb += NB) {
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        ok[j] = error_of<DG, DT>(lane_elem<DG>(gv[u], jb + j), lane_elem<DT>(tv[u], jb + j), key[j], a[j]);
-                    f(key, a, ok);
-                }
-            }
-        }
-        for (; v < nvec; v += kBlock) {
-            const u32x4 gv = buf_load<BG, kLoadNT>(grs, (int)(v * BG), 0);
-            const u32x4 tv = buf_load<BT, kLoadNT>(trs, (int)(v * BT), 0);
-#pragma unroll
-            for (int jb = 0; jb < VEC; jb += NB) {
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    ok[j] = error_of<DG, DT>(lane_elem<DG>(gv, jb + j), lane_elem<DT>(tv, jb + j), key[j], a[j]);
-                f(key, a, ok);
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 1; j < NB; ++j) ok[j] = false;
-    for (uint32_t i = nvec * VEC + threadIdx.x; i < len; i += kBlock) {
-        ok[0] = error_of<DG, DT>(load_elem<DG>(gbase, i), load_elem<DT>(tbase, i), key[0], a[0]);
-        f(key, a, ok);
-    }
-}
-
-// Block sum of one binary64 per thread in a fixed order (wave butterflies,
-// then the waves in order); the result is valid in thread 0.
-__device__ __forceinline__ double block_sum(double x, double *red) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    double s = 0.0;
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) s += red[w];
-    }
-    return s;
-}
-
-// Adds the block's per-thread integers (each below 2^64) into the pair's
-// 128-bit exact sum: wave sums in 128 bits, one atomic pair per wave.
-__device__ __forceinline__ void block_add128(uint64_t x, uint64_t *dst) {
-    uint64_t lo = x, hi = 0;
+// Wave sum of a 128-bit integer.
+__device__ __forceinline__ void wave_add128(uint64_t &lo, uint64_t &hi) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         const uint64_t ol = __shfl_xor(lo, o), oh = __shfl_xor(hi, o);
@@ -265,45 +187,403 @@ __device__ __forceinline__ void block_add128(uint64_t x, uint64_t *dst) {
         hi += oh + (s < lo ? 1u : 0u);
         lo = s;
     }
+}
+
+// Adds the block's per-thread integers (each below 2^64) into a 128-bit
+// exact sum: wave sums in 128 bits, one atomic pair per wave.
+__device__ __forceinline__ void block_add128(uint64_t x, uint64_t *dst) {
+    uint64_t lo = x, hi = 0;
+    wave_add128(lo, hi);
     if ((threadIdx.x & 63) == 0) atomic_add128(dst, lo, hi);
 }
 
-// Adds the block's LDS histogram to the pair's device histogram.
-__device__ __forceinline__ void flush_hist(const uint32_t *h, int nb, uint64_t *H) {
+// ---- selection among the bins of a histogram -------------------------------------
+struct Sel {
+    int bin;                     // the bin holding the need-th largest (-1: fewer in all)
+    uint64_t above;              // counted above it
+    uint64_t wsum[kBigWaves];
+};
+// A histogram of NB bins scanned from its top bin down by a block of NT: thread
+// t holds bins NB - 1 - t SEG and the SEG - 1 below, and what is counted above
+// them.  Its picks then cost two barriers each.
+template <int NT, int NB, typename V>
+struct Scan {
+    static constexpr int SEG = NB / NT, NW = NT / 64;
+    V c[SEG], above, total;
+    template <typename F>
+    __device__ __forceinline__ void take(Sel &sel, F &&count) {   // count(b) reads a bin
+        const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+        V x = 0;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) {
+            c[i] = count(NB - 1 - t * SEG - i);
+            x += c[i];
+        }
+        V incl = x;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const V y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) sel.wsum[wave] = incl;
+        __syncthreads();
+        V base = 0;
+        total = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const V s = (V)sel.wsum[w];
+            base += w < wave ? s : 0;
+            total += s;
+        }
+        above = base + incl - x;
+    }
+    // The bin holding the need-th largest counted value, for every thread
+    // (sel may be used again after the caller's next barrier).
+    __device__ __forceinline__ void pick(Sel &sel, V need) const {
+        __syncthreads();
+        if (threadIdx.x == 0 && (need == 0 || need > total)) sel.bin = -1;
+        V acc = above;
+        bool here = false;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) {
+            if (!here && need > acc && need <= acc + c[i]) {
+                sel.bin = NB - 1 - (int)threadIdx.x * SEG - i;
+                sel.above = acc;
+                here = true;
+            }
+            acc += c[i];
+        }
+        __syncthreads();
+    }
+};
+
+// ---- records -------------------------------------------------------------------
+// The value of the exact sums of binades b >= d0, T's `need` copies added to
+// d0's, by a block of kBig: thread t takes binades t and t + 1024, then
+// butterflies and the waves in order; valid in thread 0.
+__device__ __forceinline__ double binade_sums(const uint64_t *xs, uint64_t need, uint64_t T, int d0, double *red) {
+    constexpr int N = kBins0 / kBig;
+    uint64_t xl[N], xh[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        // (device scope: the block's own atomics are seen)
+        const uint64_t *x = xs + 2 * (threadIdx.x + i * kBig);
+        xl[i] = __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        xh[i] = __hip_atomic_load(x + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int b = threadIdx.x + i * kBig;
+        unsigned __int128 x = ((unsigned __int128)xh[i] << 64) | xl[i];
+        if (b == d0) x += (unsigned __int128)need * signif(T, d0);
+        if (b < d0 || x == 0) continue;
+        const double xd = (double)(uint64_t)(x >> 64) * 0x1p64 + (double)(uint64_t)x;
+        v += __builtin_ldexp(xd, (b != 0 ? b : 1) - 1075);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int b = threadIdx.x; b < nb; b += kBlock)
-        if (h[b]) atomicAdd((unsigned long long *)&H[b], (unsigned long long)h[b]);
+    double s = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < kBigWaves; ++w) s += red[w];
+    return s;
 }
 
-// ---- LDS gather table ----------------------------------------------------------
+// The record of a pair whose k-th largest error has key T, of which `need`
+// copies are taken; sum is the sum of the k largest.
+__device__ __forceinline__ void write_record(peat_topk_t *out, uint64_t nv, uint64_t k, uint64_t need, uint64_t T,
+                                             double sum) {
+    const double qnan = opaque_double(0x7FF80000u, 0u);
+    const double inf = opaque_double(0x7FF00000u, 0u);
+    const bool over = (T >> 52) == (uint64_t)(kBins0 - 1);    // the k-th largest error is infinite
+    peat_topk_t o;
+    o.n_valid = (int64_t)nv;
+    o.k = (int64_t)k;
+    o.count_above = k == 0 ? 0 : (int64_t)(k - need);
+    o.kth_value = k == 0 ? qnan : (over ? inf : key_value(T));
+    o.sum_topk = k == 0 ? 0.0 : (over ? inf : sum);
+    o.mean_topk = k == 0 ? qnan : (over ? inf : sum / (double)k);
+    *out = o;
+}
+
+// ---- start -----------------------------------------------------------------------
+// B bytes at p (any alignment) as 32-bit words.
+template <int B>
+__device__ __forceinline__ void load_words(const char *p, uint32_t (&w)[B / 4]) {
+    typedef uint32_t any4 __attribute__((ext_vector_type(4), aligned(1)));
+    typedef __attribute__((address_space(1))) const any4 gany4_t;
+#pragma unroll
+    for (int i = 0; i < B / 16; ++i) {
+        const any4 v = ((gany4_t *)p)[i];
+        w[4 * i] = v.x;
+        w[4 * i + 1] = v.y;
+        w[4 * i + 2] = v.z;
+        w[4 * i + 3] = v.w;
+    }
+}
+template <int DT, int NW>
+__device__ __forceinline__ auto run_elem(const uint32_t (&w)[NW], int j) {
+    if constexpr (Tr<DT>::W == 64)
+        return (uint64_t)w[2 * j] | ((uint64_t)w[2 * j + 1] << 32);
+    else if constexpr (Tr<DT>::W == 32)
+        return w[j];
+    else
+        return (w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
+}
+
+// The thread's keys (kEmpty: none): runs of consecutive errors, all of the
+// pair's when it is small, else one run per span of n / kRuns elements, at a
+// scrambled place of the span.
+template <int DG, int DT>
+__device__ __forceinline__ void load_keys(const SigDesc &d, uint64_t (&key)[kKeys]) {
+    constexpr int SG = Tr<DG>::W / 8, ST = Tr<DT>::W / 8;
+    const char *g = static_cast<const char *>(d.g);
+    const char *t = static_cast<const char *>(d.t);
+    const bool all = d.n <= kSmallN;
+#pragma unroll
+    for (int q = 0; q < kKeys / kRun; ++q) {
+        const uint32_t run = (uint32_t)(q * kBig + threadIdx.x);
+        int64_t at = (int64_t)run * kRun;
+        if (!all) {
+            const int64_t a = (int64_t)run * d.n / kRuns, b = (int64_t)(run + 1) * d.n / kRuns;
+            at = a + (int64_t)__umul64hi((uint64_t)(run + 1) * 0x9E3779B97F4A7C15ull, (uint64_t)(b - a - kRun + 1));
+        }
+        uint64_t x;
+        double a;
+        if (at + kRun <= d.n) {
+            uint32_t gw[kRun * SG / 4], tw[kRun * ST / 4];
+            load_words<kRun * SG>(g + at * SG, gw);
+            load_words<kRun * ST>(t + at * ST, tw);
+#pragma unroll
+            for (int j = 0; j < kRun; ++j)
+                key[q * kRun + j] = error_of<DG, DT>(run_elem<DG>(gw, j), run_elem<DT>(tw, j), x, a) ? x : kEmpty;
+        } else {
+#pragma unroll
+            for (int j = 0; j < kRun; ++j) {
+                key[q * kRun + j] = kEmpty;
+                if (at + j < d.n && error_of<DG, DT>(load_elem<DG>(g, at + j), load_elem<DT>(t, at + j), x, a))
+                    key[q * kRun + j] = x;
+            }
+        }
+    }
+}
+static_assert(kSmallN / kRuns >= kRun, "a sampled run fits its span");
+
+struct StartShared {
+    uint32_t h[kCopies * kCopyStride];
+    Sel sel;
+    double red[kBigWaves];
+    uint64_t xl[kBigWaves], xh[kBigWaves];
+    uint32_t n[kBigWaves];
+};
+
+// Block total of a count per thread.
+__device__ __forceinline__ uint32_t block_count(uint32_t x, uint32_t *red) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+    __syncthreads();
+    uint32_t s = 0;
+    for (int w = 0; w < kBigWaves; ++w) s += red[w];
+    return s;
+}
+
+// Counts digit `level` of the keys on the prefix (key >> pshift == prefix)
+// into h.
+__device__ __forceinline__ void digit_hist(uint32_t (&h)[kCopies * kCopyStride], const uint64_t (&key)[kKeys], int level,
+                                           int pshift, uint64_t prefix) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < kCopies * kCopyStride; i += kBig) h[i] = 0;
+    __syncthreads();
+    uint32_t *c = h + (threadIdx.x & (kCopies - 1)) * kCopyStride;
+#pragma unroll
+    for (int j = 0; j < kKeys; ++j)
+        if (key[j] != kEmpty && (level == 0 || (key[j] >> pshift) == prefix)) atomicAdd(&c[digit_of(key[j], level)], 1u);
+    __syncthreads();
+}
+typedef Scan<kBig, kBins0, uint32_t> KeyScan;
+__device__ __forceinline__ void digit_scan(KeyScan &scan, Sel &sel, const uint32_t (&h)[kCopies * kCopyStride]) {
+    scan.take(sel, [&](int b) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int q = 0; q < kCopies; ++q) c += h[q * kCopyStride + b];
+        return c;
+    });
+}
+
+__global__ void __launch_bounds__(kBig) topk_start(TopkParams P) {
+    __shared__ StartShared sh;
+    const int pair = blockIdx.x, tid = threadIdx.x;
+    const SigDesc d = desc_of(P, pair);
+    if (pair == 0 && tid == 0) {
+        P.fill[0] = 0;
+        P.fill[1] = 0;
+        *P.open = 0;
+    }
+    if (d.n > kSmallN) {
+        if (tid < 2) P.counts[2 * pair + tid] = 0;
+        if (tid == 0) P.ovf[pair] = 0;
+        for (int i = tid; i < 2 * kBins0; i += kBig) P.xsum[(size_t)pair * 2 * kBins0 + i] = 0;
+    }
+    uint64_t key[kKeys];
+    if (d.n > 0) {
+        static_assert(kKindTypes[3][1] == PEAT_F64 && kKindTypes[9][0] == PEAT_BF16, "kind table order");
+        switch (d.dtype * 4 + d.tdtype) {                     // uniform
+            case PEAT_F32 * 4 + PEAT_F32: load_keys<PEAT_F32, PEAT_F32>(d, key); break;
+            case PEAT_F16 * 4 + PEAT_F16: load_keys<PEAT_F16, PEAT_F16>(d, key); break;
+            case PEAT_BF16 * 4 + PEAT_BF16: load_keys<PEAT_BF16, PEAT_BF16>(d, key); break;
+            case PEAT_F32 * 4 + PEAT_F64: load_keys<PEAT_F32, PEAT_F64>(d, key); break;
+            case PEAT_F32 * 4 + PEAT_F16: load_keys<PEAT_F32, PEAT_F16>(d, key); break;
+            case PEAT_F32 * 4 + PEAT_BF16: load_keys<PEAT_F32, PEAT_BF16>(d, key); break;
+            case PEAT_F16 * 4 + PEAT_F32: load_keys<PEAT_F16, PEAT_F32>(d, key); break;
+            case PEAT_BF16 * 4 + PEAT_F32: load_keys<PEAT_BF16, PEAT_F32>(d, key); break;
+            case PEAT_F16 * 4 + PEAT_F64: load_keys<PEAT_F16, PEAT_F64>(d, key); break;
+            default: load_keys<PEAT_BF16, PEAT_F64>(d, key); break;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kKeys; ++j) key[j] = kEmpty;
+    }
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kKeys; ++j) mine += key[j] != kEmpty ? 1u : 0u;
+    const uint64_t nv = block_count(mine, sh.n);
+    const uint64_t k = top_count(nv, P);
+    KeyScan scan0, scan1;                                     // of digit 0, of a later digit
+    if (k != 0) {
+        digit_hist(sh.h, key, 0, 0, 0);
+        digit_scan(scan0, sh.sel, sh.h);
+        scan0.pick(sh.sel, (uint32_t)k);
+    }
+    const int b0 = k != 0 ? sh.sel.bin : 0;
+    const uint64_t above0 = k != 0 ? sh.sel.above : 0;
+
+    if (d.n <= kSmallN) {
+        // every error is here: the other digits, the sum and the record
+        uint64_t T = (uint64_t)b0 << 52, need = k - above0;
+        if (k != 0 && b0 != kBins0 - 1 && (b0 != 0 || d.tdtype == PEAT_F64)) {
+            for (int L = 1; L < kTopkLevels; ++L) {
+                digit_hist(sh.h, key, L, digit_shift(L - 1), T >> digit_shift(L - 1));
+                digit_scan(scan1, sh.sel, sh.h);
+                scan1.pick(sh.sel, (uint32_t)need);
+                T |= (uint64_t)sh.sel.bin << digit_shift(L);
+                need -= sh.sel.above;
+            }
+        }
+        // the errors of T's binade above it exactly, those of the binades
+        // above lane by lane, butterflies and waves in order
+        const uint64_t end = (uint64_t)(b0 + 1) << 52;
+        double s = 0.0;
+        uint64_t xl = 0, xh = 0;
+#pragma unroll
+        for (int j = 0; j < kKeys; ++j) {
+            if (key[j] == kEmpty) continue;
+            if (key[j] >= end)
+                s += key_value(key[j]);
+            else if (key[j] > T)
+                xl += signif(key[j], b0);                     // at most 16 below 2^53
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+        wave_add128(xl, xh);
+        if ((tid & 63) == 0) {
+            sh.red[tid >> 6] = s;
+            sh.xl[tid >> 6] = xl;
+            sh.xh[tid >> 6] = xh;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            unsigned __int128 x = (unsigned __int128)need * signif(T, b0);
+            double t = 0.0;
+            for (int w = 0; w < kBigWaves; ++w) {
+                t += sh.red[w];
+                x += ((unsigned __int128)sh.xh[w] << 64) | sh.xl[w];
+            }
+            const double xd = (double)(uint64_t)(x >> 64) * 0x1p64 + (double)(uint64_t)x;
+            write_record(P.outs + pair, nv, k, need, T, t + __builtin_ldexp(xd, (b0 != 0 ? b0 : 1) - 1075));
+            P.state[pair].status = kTopkDone;
+        }
+        return;
+    }
+
+    // A large pair: the window from the sample's errors of ranks k + m and
+    // k - m, 22 bits of each; below the first nonzero key only 0 is left, and
+    // above the last rank +Inf.  m is five standard deviations of the number
+    // of sampled errors at or above the k-th, from its variance between runs
+    // (errors of one run may be alike), plus 2.
+    TopkState st;
+    st.status = kTopkWindow;
+    st.append = 0;
+    st.wlo = 1;
+    st.whi = ((uint64_t)(kBins0 - 1) << 52) + 1;
+    if (k != 0) {
+        uint64_t digit1 = ~uint64_t(0);                       // the binade that scan1 covers
+        auto end_of = [&](uint64_t rank) {                    // the 22-bit bin of a rank
+            scan0.pick(sh.sel, (uint32_t)rank);
+            const uint64_t b = (uint64_t)sh.sel.bin, in = rank - sh.sel.above;
+            if (b != digit1) {
+                digit_hist(sh.h, key, 1, 52, b);
+                digit_scan(scan1, sh.sel, sh.h);
+                digit1 = b;
+            }
+            scan1.pick(sh.sel, (uint32_t)in);
+            return (b << 11) + (uint64_t)sh.sel.bin;
+        };
+        const uint64_t at = end_of(k);
+        uint32_t c1 = 0, c2 = 0;
+#pragma unroll
+        for (int q = 0; q < kKeys; q += kRun) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int j = q; j < q + kRun; ++j) c += key[j] != kEmpty && (key[j] >> 41) >= at ? 1u : 0u;
+            c1 += c;
+            c2 += c * c;
+        }
+        const double t1 = (double)block_count(c1, sh.n), t2 = (double)block_count(c2, sh.n);
+        const double var = t2 - t1 * t1 / (double)kRuns;      // of the runs' total
+        const uint64_t m = (uint64_t)(5.0 * __builtin_sqrt(var > 0.0 ? var : 0.0)) + 2;
+        if (k + m <= nv) st.wlo = max(end_of(k + m) << 41, uint64_t(1));
+        if (k > m) st.whi = min((end_of(k - m) + 1) << 41, st.whi);
+        // a window of zero errors alone has nothing to gather
+        if (k > m && st.whi <= (uint64_t(1) << 41) && d.tdtype != PEAT_F64) st.whi = st.wlo = 1;
+    }
+    // do the window's errors repeat?  (every fourth key, counted by hash)
+    __syncthreads();
+    for (int i = tid; i < kBins0; i += kBig) sh.h[i] = 0;
+    __syncthreads();
+    uint32_t w = 0;
+#pragma unroll
+    for (int j = 0; j < kKeys; j += 4)
+        if (key[j] >= st.wlo && key[j] < st.whi) {
+            ++w;
+            sh.h[(uint32_t)((key[j] * 0x9E3779B97F4A7C15ull) >> 53)] = 1;
+        }
+    __syncthreads();
+    uint32_t z = 0;
+    for (int i = tid; i < kBins0; i += kBig) z += sh.h[i];
+    const uint32_t seen = block_count(w, sh.n), distinct = block_count(z, sh.n);
+    st.append = seen >= 32 && distinct * 2 > (seen < 1024u ? seen : 1024u) ? 1 : 0;
+    if (tid == 0) P.state[pair] = st;
+}
+
+// ---- gather ----------------------------------------------------------------------
 struct Table {
     uint64_t key[kTable];
     uint32_t cnt[kTable];
-    uint32_t full;               // some key found no slot
     uint32_t n;                  // occupied slots (flush)
     uint32_t pos;                // entries written (flush)
     uint32_t ok;                 // the flush fits the buffer
     unsigned long long base;
 };
 
-__device__ __forceinline__ void table_init(Table &t) {
-    for (int i = threadIdx.x; i < kTable; i += kBlock) {
-        t.key[i] = kEmpty;
-        t.cnt[i] = 0;
-    }
-    if (threadIdx.x == 0) {
-        t.full = 0;
-        t.n = 0;
-        t.pos = 0;
-    }
-}
-
 // Counts key in the table (open addressing, slots go from empty to one key
 // only); false when its probe sequence is full of other keys.
 __device__ __forceinline__ uint32_t table_slot(uint64_t key) {
     return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> 55);                 // 9 bits
 }
-
 __device__ __forceinline__ bool table_count(Table &t, uint64_t key) {
     const uint32_t h = table_slot(key);
 #pragma unroll 1
@@ -320,782 +600,598 @@ __device__ __forceinline__ bool table_count(Table &t, uint64_t key) {
     return false;
 }
 
-// Writes the table's keys as entries of `pair` into region r, or marks the
-// pair (flag r) when a key found no slot or the region is full; positions
-// handed out past the region's end are left to later overflows, positions
-// inside it that this block cannot use are marked unused.
-__device__ __forceinline__ void table_flush(Table &t, const TopkParams &P, int r, int pair, int round,
-                                            bool window) {
-    __syncthreads();
-    for (int i = threadIdx.x; i < kTable; i += kBlock)
-        if (t.cnt[i]) atomicAdd(&t.n, 1u);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        // positions are taken only for a complete table; taken positions that
-        // run past the region's end are given back as unused entries
-        uint32_t n = t.full ? 0u : t.n;
-        unsigned long long base = 0;
-        uint32_t ok = t.full == 0;
-        if (n > 0) {
-            base = atomicAdd(&P.fill[r], (unsigned long long)n);
-            if (base + n > P.cap[r]) ok = 0;
-        }
-        if (!ok) {
-            P.ovf[2 * pair + r] = 1;
-            P.ovf[2 * P.count + (window ? 2 : r)] = 1;
-        }
-        t.base = base;
-        t.ok = ok;
-        t.n = n;
-    }
-    __syncthreads();
-    TopkEntry *E = P.ents + (r ? P.cap[0] : 0);
-    const unsigned long long base = t.base;
-    if (t.ok) {
-        for (int i = threadIdx.x; i < kTable; i += kBlock)
-            if (t.cnt[i]) {
-                const uint32_t q = atomicAdd(&t.pos, 1u);
-                E[base + q] = TopkEntry{t.key[i], t.cnt[i], entry_tag(pair, round)};
-            }
-    } else {
-        const unsigned long long end = base + t.n < P.cap[r] ? base + t.n : P.cap[r];
-        for (unsigned long long q = base + threadIdx.x; q < end; q += kBlock) E[q] = TopkEntry{0, 0, -1};
-    }
-}
+struct GatherShared {
+    Table tab;
+    uint64_t list[kWaves][kTopkSeg + 64];       // the waves' keys on their way to the pool
+    uint64_t queue[kWaves][128];                // errors to look at closely (golden and test, or the error itself)
+    // significand sums of the errors above the window, binades from the
+    // window's up: low 32 bits and the rest apart (no overflow in a chunk)
+    unsigned long long xl[kSumBins], xh[kSumBins];
+    uint32_t cnt[kWaves][2];
+};
 
-// Appends (key, 1) entries of keys that found no slot to region 1, one
-// atomic per wave; a wave past the region's end marks the pair.
-__device__ __forceinline__ void spill_entry(bool take, uint64_t key, const TopkParams &P, int pair, int round) {
-    const uint64_t m = __ballot(take);
-    if (m == 0) return;
-    const int leader = __ffsll((long long)m) - 1;
-    unsigned long long base = 0;
-    if ((int)(threadIdx.x & 63) == leader) base = atomicAdd(&P.fill[1], (unsigned long long)__popcll(m));
-    base = __shfl(base, leader);
-    if (take) {
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        const unsigned long long q = base + rank;
-        if (q < P.cap[1]) {
-            P.ents[P.cap[0] + q] = TopkEntry{key, 1u, entry_tag(pair, round)};
+// A wave's list of single keys: full segments go to the pool (the segment's
+// number to the chunk's directory).  Every member is uniform over the wave.
+struct WaveList {
+    uint32_t n, nseg;
+    bool lost;                                  // a segment found no room
+    __device__ __forceinline__ void put(const TopkParams &P, uint64_t (&buf)[kTopkSeg + 64], TopkDir &dir, int wave,
+                                        bool take, uint64_t key) {
+        const uint64_t m = __ballot(take);
+        if (m == 0) return;
+        if (take) {
+            const uint32_t r = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            buf[n + r] = key;
+        }
+        n += (uint32_t)__popcll(m);
+        if (n >= kTopkSeg) flush(P, buf, dir, wave, kTopkSeg);
+    }
+    __device__ __forceinline__ void flush(const TopkParams &P, uint64_t (&buf)[kTopkSeg + 64], TopkDir &dir, int wave,
+                                          uint32_t cnt) {
+        const uint32_t lane = threadIdx.x & 63;
+        uint32_t seg = ~0u;
+        if (nseg < kTopkSegs && !lost) {
+            unsigned long long s = 0;
+            if (lane == 0) s = atomicAdd(&P.fill[1], 1ull);
+            const uint64_t u = uniform64(s);
+            if (u < P.cap[1] / kTopkSeg) seg = (uint32_t)u;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (seg == ~0u) {
+            lost = true;
         } else {
-            P.ovf[2 * pair + 1] = 1;
-            P.ovf[2 * P.count + 1] = 1;
+            uint64_t *dst = P.pool + (uint64_t)seg * kTopkSeg;
+            for (uint32_t i = lane; i < cnt; i += 64) dst[i] = buf[i];
+            if (lane == 0) dir.seg[wave][nseg] = seg;
+            ++nseg;
         }
+        // what is left over (fewer than 64 keys) moves to the front
+        const uint64_t rest = buf[cnt + lane < kTopkSeg + 64 ? cnt + lane : 0];
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        n -= cnt;
+        if (lane < n) buf[lane] = rest;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
-}
+};
 
-// ---- level 0 ----------------------------------------------------------------
-// Status after level 0 resolved to binade b: an infinite boundary fixes the
-// k-th largest error already, and so does binade 0 when it holds only zero
-// errors; with a binary64 test side it also holds the subnormal errors,
-// which the next levels order like any other binade.
-__device__ __forceinline__ void level0_status(TopkState &st, int b, int tdtype) {
-    st.d0 = b;
-    st.level = 0;
-    const bool zero_only = b == 0 && tdtype != PEAT_F64;
-    st.status = (zero_only || b == kBins0 - 1) ? kTopkDone : kTopkActive;
-}
-
-// Level 0 from the pair's signature, which counts the same errors of the same
-// valid pairs.  Bin i of the record covers the error keys from that of
-// 2^(lo + i w) up to that of 2^(lo + (i + 1) w); with one-binade bins (w = 1)
-// a regular bin is binade field lo + i + 1023 and fixes level 0.  A wider bin,
-// the under bin (keys 1 up to that of 2^lo) or the over bin (from 2^hi up,
-// +Inf included) leaves a window of binades, which the gathering pass
-// collects whole.  Errors below every bin are the zero errors alone when the
-// test side is not binary64 (a difference of two narrower values is a
-// multiple of 2^-149, far above the subnormal range): the k-th largest error
-// is then 0.  Leaves the state open when the record does not match the pair.
-__device__ void level0_from_sig(const peat_signature_t &g, const SigDesc &d, const TopkParams &P,
-                                TopkState &st) {
-    if (g.n != d.n || g.n_valid < 0) return;
-    uint64_t tot = (uint64_t)g.hist_zero + (uint64_t)g.hist_under + (uint64_t)g.hist_over;
-    for (int i = 0; i < P.nbins; ++i) tot += (uint64_t)g.hist[i];
-    if (tot != (uint64_t)g.n_valid) return;
-    const uint64_t nv = (uint64_t)g.n_valid;
-    const uint64_t k = (uint64_t)(((unsigned __int128)nv * (uint32_t)P.num + (uint32_t)P.den - 1) / (uint32_t)P.den);
-    st.n_valid = nv;
-    st.k = k;
-    if (k == 0) {
-        st.level = 0;
-        st.status = kTopkDone;
-        st.d0 = 0;
-        return;
-    }
-    auto key_of = [](int e) { return (uint64_t)(e + 1023) << 52; };      // key of 2^e
-    uint64_t acc = 0;
-    auto window = [&](uint64_t lo, uint64_t hi, uint64_t c) {
-        st.need = k - acc;
-        st.cand = c;
-        st.wlo = lo;
-        st.whi = hi;
-        st.level = -2;
-        st.status = kTopkActive;
-    };
-    const uint64_t over = (uint64_t)g.hist_over;
-    if (k <= over) {
-        window(key_of(P.hi), uint64_t(1) << 63, over);
-        return;
-    }
-    acc = over;
-    const int w = (P.hi - P.lo) / P.nbins;
-    for (int i = P.nbins - 1; i >= 0; --i) {
-        const uint64_t c = (uint64_t)g.hist[i];
-        if (acc + c >= k) {
-            if (w == 1) {
-                st.need = k - acc;
-                st.cand = c;
-                st.key = key_of(P.lo + i);
-                level0_status(st, P.lo + i + 1023, d.tdtype);
-            } else {
-                window(key_of(P.lo + i * w), key_of(P.lo + (i + 1) * w), c);
-            }
-            return;
-        }
-        acc += c;
-    }
-    const uint64_t under = (uint64_t)g.hist_under;
-    if (k <= acc + under) {
-        window(1, key_of(P.lo), under);
-        return;
-    }
-    acc += under;
-    if (d.tdtype == PEAT_F64) return;
-    st.need = k - acc;
-    st.cand = (uint64_t)g.hist_zero;
-    st.key = 0;
-    level0_status(st, 0, d.tdtype);
-}
-
-__global__ void __launch_bounds__(kBlock) topk_init(TopkParams P) {
-    const int pair = blockIdx.x * kBlock + threadIdx.x;
-    if (pair == 0) {
-        P.fill[0] = 0;
-        P.fill[1] = 0;
-        P.ovf[2 * P.count] = 0;
-        P.ovf[2 * P.count + 1] = 0;
-        P.ovf[2 * P.count + 2] = 0;
-    }
-    if (pair >= P.count) return;
-    P.ovf[2 * pair] = 0;
-    P.ovf[2 * pair + 1] = 0;
-    P.counts[2 * pair] = 0;
-    P.counts[2 * pair + 1] = 0;
-    TopkState st;
-    st.n_valid = 0;
-    st.k = 0;
-    st.need = 0;
-    st.cand = 0;
-    st.key = 0;
-    st.wlo = 0;
-    st.whi = 0;
-    st.level = -1;
-    st.status = kTopkActive;
-    st.d0 = 0;
-    st.round = 0;
-    st.sampled = 0;
-    st.reserved = 0;
-    if (P.sigs) level0_from_sig(P.sigs[pair], P.descs[pair], P, st);
-    P.state[pair] = st;
-}
-
-// ---- a window from a sample ----------------------------------------------------
-constexpr int kSampleRuns = 256;                // one run of consecutive elements per thread
-constexpr int kSampleRun = 32;
-constexpr int64_t kSampleMinN = int64_t(1) << 16;
-constexpr int kSampleSet = 8192;                // LDS hash set of the sample's window keys
-constexpr int kSampleMaxDistinct = 256;         // more distinct sampled keys in the binade: no guess
-
-// One block per open pair of this kind (n >= 2^16): errors of 256 runs of 32
-// consecutive elements spread over the pair, and the binade of the sample's
-// k-th largest error as a guess of binade D0 -- unless it holds zero or
-// infinite errors, or its sampled errors take more than 256 distinct values
-// (the gathering pass would not fit them).  Pass A then gathers that binade
-// and counts the pair's valid errors and those above it, which confirm the
-// guess exactly; a wrong guess costs the binade pass and a second gathering
-// pass over the pair.  A right guess gives the records of the binade-pass
-// route.
+// One chunk per block.  Where both sides fit binary32 the comparison with the
+// window's start is made there: rounding is monotone, so an error of at least
+// wlo has a binary32 difference of at least thr, the binary32 value below wlo
+// (NaN compares as not below).
 template <int DG, int DT>
-__global__ void __launch_bounds__(kBlock) topk_sample(TopkParams P) {
-    const int pair = blockIdx.x;
-    const SigDesc d = P.descs[pair];
-    if (d.dtype != DG || d.tdtype != DT || d.n < kSampleMinN) return;
-    TopkState st = P.state[pair];
-    if (st.level != -1) return;
-    __shared__ uint32_t h[kBins0];
-    __shared__ uint64_t set[kSampleSet];
-    __shared__ uint32_t nvalid, distinct;
-    __shared__ int bs;
-    for (int b = threadIdx.x; b < kBins0; b += kBlock) h[b] = 0;
-    for (int i = threadIdx.x; i < kSampleSet; i += kBlock) set[i] = kEmpty;
-    if (threadIdx.x == 0) {
-        nvalid = 0;
-        distinct = 0;
-    }
-    __syncthreads();
-    constexpr int ESZG = Tr<DG>::W / 8, ESZT = Tr<DT>::W / 8;
-    const char *g = static_cast<const char *>(d.g);
-    const char *t = static_cast<const char *>(d.t);
-    int64_t start = (int64_t)threadIdx.x * d.n / kSampleRuns;
-    if (start > d.n - kSampleRun) start = d.n - kSampleRun;
-    uint64_t keys[kSampleRun];
-    uint32_t mine = 0;
-#pragma unroll
-    for (int i = 0; i < kSampleRun; ++i) {
-        double a;
-        const bool ok = error_of<DG, DT>(load_elem<DG>(g + start * ESZG, (uint32_t)i),
-                                         load_elem<DT>(t + start * ESZT, (uint32_t)i), keys[i], a);
-        if (!ok) keys[i] = kEmpty;
-        else {
-            ++mine;
-            atomicAdd(&h[keys[i] >> 52], 1u);
-        }
-    }
-    atomicAdd(&nvalid, mine);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint64_t ks = ((uint64_t)nvalid * (uint32_t)P.num + (uint32_t)P.den - 1) / (uint32_t)P.den;
-        int b = -1;
-        uint64_t acc = 0;
-        if (ks > 0)
-            for (b = kBins0 - 1; b > 0 && acc + h[b] < ks; --b) acc += h[b];
-        bs = b;
-    }
-    __syncthreads();
-    const int b = bs;
-    if (b < 1 || b > kBins0 - 2) return;                      // no sample boundary, or zero or infinite errors
-    const uint64_t wlo = (uint64_t)b << 52, whi = (uint64_t)(b + 1) << 52;
-    // distinct sampled keys inside the binade
-#pragma unroll
-    for (int i = 0; i < kSampleRun; ++i) {
-        const uint64_t key = keys[i];
-        if (key == kEmpty || key < wlo || key >= whi) continue;
-        uint32_t slot = (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> 51);   // 13 bits
-#pragma unroll 1
-        for (int p = 0; p < kSampleSet; ++p, slot = (slot + 1) & (kSampleSet - 1)) {
-            const uint64_t old = atomicCAS((unsigned long long *)&set[slot], (unsigned long long)kEmpty,
-                                           (unsigned long long)key);
-            if (old == kEmpty) {
-                atomicAdd(&distinct, 1u);
-                break;
-            }
-            if (old == key) break;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x != 0 || distinct > kSampleMaxDistinct) return;
-    st.wlo = wlo;
-    st.whi = whi;
-    st.level = -2;
-    st.status = kTopkActive;
-    st.sampled = 1;
-    st.k = ~uint64_t(0);                                       // counted by pass A
-    st.n_valid = 0;
-    st.need = 0;
-    st.cand = 0;
-    P.state[pair] = st;
-}
-
-// ---- streaming passes over the tensors ----------------------------------------
-enum { kPass1 = 0, kPassA = 1, kPassC = 2, kPassT = 3 };
-
-// pass 1: binade histogram of the pairs whose level 0 is open (one chunk per block)
-template <int DG, int DT>
-__device__ __forceinline__ void pass1_chunk(const TopkParams &P, int64_t gchunk, uint32_t *h) {
-    const int pair = P.chunk_pair[gchunk];
-    if (P.state[pair].level != -1) return;
-    const SigDesc d = P.descs[pair];
-    for (int b = threadIdx.x; b < kBins0; b += kBlock) h[b] = 0;
-    __syncthreads();
-    for_each_error<DG, DT>(d, gchunk - d.first_chunk, [&](uint64_t key, double) { atomicAdd(&h[key >> 52], 1u); });
-    flush_hist(h, kBins0, P.hist + (size_t)pair * kTopkBins);
-}
-
-// pass A (one chunk per block in round 0; round 1 serves the pairs whose
-// window did not fit, after their binade pass).  Sums the errors above the
-// gathered range and gathers the range: binade D0, or the pair's window.
-// For binade D0 each error is counted once: in the gather table, or (once a
-// key of this thread found no slot) in the digit-1 histogram; at the end the
-// table's counts go into that histogram too (in LDS when the block
-// overflowed, else straight to the pair's).  A window that does not fit is
-// given up (the pair is gathered again by binade).
-template <int DG, int DT>
-__device__ __forceinline__ void passA_chunk(const TopkParams &P, int64_t gchunk, uint32_t *h, Table &tab, double *red) {
-    const int pair = P.chunk_pair[gchunk];
+__global__ void __launch_bounds__(kBlock) topk_gather(TopkParams P) {
+    __shared__ GatherShared sh;
+    const int64_t gchunk = P.chunk_base + blockIdx.x;
+    const int pair = pair_of(P, gchunk);
     const TopkState st = P.state[pair];
-    if (st.round != P.round) return;                          // served by the other round
-    // nothing above an infinite boundary; nothing at all when k = 0
-    if (st.k == 0 || (st.level >= 0 && st.d0 == kBins0 - 1)) {
-        if (threadIdx.x == 0) P.part_a[gchunk] = 0.0;
-        return;
+    if (st.status != kTopkWindow) return;
+    const SigDesc d = desc_of(P, pair);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = (int)__builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
+    constexpr bool kDiff32 = Tr<DG>::W <= 32 && Tr<DT>::W <= 32;
+    Table &tab = sh.tab;
+    TopkDir &dir = P.dir[gchunk];
+    const uint64_t wlo = uniform64(st.wlo), whi = uniform64(st.whi);
+    const bool table = st.append == 0;
+    const int base = (int)(wlo >> 52);                        // binade of LDS sum 0
+    const double lo = key_value(wlo);
+    // (to nearest is at most one step above; an error that is not 0 is at least
+    // the least binary32 value there, which keeps zero errors out)
+    const uint32_t near_lo = __float_as_uint(lo > 0x1.fffffep127 ? 0x1.fffffep127f : (float)lo);
+    const float thr = __uint_as_float(near_lo > 3u ? near_lo - 2u : 1u);
+    for (int i = tid; i < kTable; i += kBlock) {
+        tab.key[i] = kEmpty;
+        tab.cnt[i] = 0;
     }
-    const SigDesc d = P.descs[pair];
-    const bool win = st.level == -2;
-    const uint64_t glo = win ? st.wlo : (uint64_t)st.d0 << 52;           // the gathered keys [glo, ghi)
-    const uint64_t ghi = win ? st.whi : (uint64_t)(st.d0 + 1) << 52;
-    const bool active = st.status == kTopkActive;            // the range needs ordering
-    const bool hist1 = active && !win;
-    const bool samp = st.sampled != 0;                        // a guessed binade: count the valid errors and those above
-    uint32_t nv = 0, na = 0;                                  // this lane's counts
-    if (active) {
-        if (hist1)
-            for (int b = threadIdx.x; b < kTopkBins; b += kBlock) h[b] = 0;
-        table_init(tab);
-        __syncthreads();
+    if (tid < kSumBins) {
+        sh.xl[tid] = 0;
+        sh.xh[tid] = 0;
     }
-    double s = 0.0;
-    bool spill = false;                                       // this thread's keys find no slot
-    for_each_error_vec<DG, DT>(d, gchunk - d.first_chunk, [&](const auto &key, const auto &a, const auto &ok) {
-        constexpr int V = sizeof(ok) / sizeof(ok[0]);
-        bool in[V];
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            if (ok[j] && key[j] >= ghi) s += a[j];
-            in[j] = ok[j] && key[j] >= glo && key[j] < ghi && active;
+    if (tid == 0) {
+        tab.n = 0;
+        tab.pos = 0;
+    }
+    __syncthreads();
+
+    uint32_t bad = 0, na = 0;                                 // wave counts: invalid, above the window
+    uint32_t qn = 0;                                          // queue length (uniform, below 64 between rows)
+    WaveList wl{0, 0, false};
+    // cnt queued errors, one per lane
+    auto work = [&](uint32_t cnt) __attribute__((always_inline)) {
+        qn -= cnt;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // entries of other lanes
+        const bool on = (uint32_t)lane < cnt;
+        const uint64_t e = sh.queue[wave][qn + (on ? lane : 0)];
+        double a;
+        bool valid;
+        if constexpr (kDiff32) {
+            const double G = (double)__uint_as_float((uint32_t)e), T = (double)__uint_as_float((uint32_t)(e >> 32));
+            valid = G == G && T == T;
+            a = G == T ? 0.0 : __builtin_fabs(T - G);
+        } else {
+            a = key_value(e);
+            valid = a == a;
         }
-        if (!spill) {
-            // first probes of the vector's keys issued together; a key found
-            // there is counted, others take the full probe sequence
-            uint32_t slot[V];
-            uint64_t cur[V];
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                slot[j] = table_slot(key[j]);
-                cur[j] = in[j] ? __hip_atomic_load(&tab.key[slot[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
-                               : kEmpty;
+        const uint64_t key = (uint64_t)__double_as_longlong(a);
+        bad += (uint32_t)__popcll(__ballot(on && !valid));
+        const bool up = on && valid && key >= whi;
+        na += (uint32_t)__popcll(__ballot(up));
+        if (up) {
+            const int b = (int)(key >> 52);
+            const uint64_t x = signif(key, b);
+            if (b - base < kSumBins) {
+                atomicAdd(&sh.xl[b - base], (unsigned long long)(uint32_t)x);
+                atomicAdd(&sh.xh[b - base], (unsigned long long)(x >> 32));
+            } else {
+                atomic_add128(P.xsum + ((size_t)pair * kBins0 + b) * 2, x, 0);
             }
+        }
+        bool in = on && valid && key >= wlo && key < whi;
+        if (table && in) in = !table_count(tab, key);
+        wl.put(P, sh.list[wave], dir, wave, in, key);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    };
+    // One element of every lane (on: the lane has one), queued unless it lies
+    // below the window.
+    auto row = [&](auto gb, auto tb, bool on) __attribute__((always_inline)) {
+        uint64_t e;
+        bool near;
+        if constexpr (kDiff32) {
+            const float g = widen32<DG>(gb), t = widen32<DT>(tb);
+            near = !(__builtin_fabsf(t - g) < thr);
+            e = (uint64_t)__float_as_uint(g) | ((uint64_t)__float_as_uint(t) << 32);
+        } else {
+            const double G = widen<DG>(gb), T = widen<DT>(tb);
+            const double a = __builtin_fabs(T - G);
+            near = !(a < lo);
+            // equal infinities differ by 0 (an error below every window)
+            near = near && !(G == T && a != a);
+            e = (uint64_t)__double_as_longlong(a);
+        }
+        near = near && on;
+        const uint64_t m = __ballot(near);
+        if (m != 0) {
+            if (near) {
+                const uint32_t r = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                sh.queue[wave][qn + r] = e;
+            }
+            qn += (uint32_t)__popcll(m);
+            if (qn >= 64) work(64);
+        }
+    };
+    const ChunkView<DG, DT> c(d, gchunk - d.first_chunk);
+    constexpr int VEC = ChunkView<DG, DT>::VEC;
+    auto vector = [&](const u32x4 &gv, const u32x4 &tv, bool on) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) {
-                if (!in[j]) continue;
-                if (cur[j] == key[j]) {
-                    atomicAdd(&tab.cnt[slot[j]], 1u);
-                    in[j] = false;
-                } else if (table_count(tab, key[j])) {
-                    in[j] = false;
-                } else {
-                    spill = true;
-                    tab.full = 1;
+        for (int j = 0; j < VEC; ++j) row(lane_elem<DG>(gv, j), lane_elem<DT>(tv, j), on);
+    };
+    constexpr int U = VEC > 4 ? 1 : 2;                        // vectors per half step
+    const uint32_t nfull = c.nvec / kBlock;                   // vectors that every lane has
+    uint32_t i = 0;
+    if (nfull >= 2 * U) {
+        // two register sets in turn: one is loaded while the other is worked
+        u32x4 ga[U], ta[U], gb[U], tb[U];
+        auto load = [&](u32x4 (&g)[U], u32x4 (&t)[U], uint32_t v) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) c.load((v + u) * kBlock + tid, g[u], t[u]);
+        };
+        load(ga, ta, 0);
+        for (; i + 2 * U <= nfull; i += 2 * U) {
+            load(gb, tb, i + U);
+#pragma unroll
+            for (int u = 0; u < U; ++u) vector(ga[u], ta[u], true);
+            load(ga, ta, i + 4 * U <= nfull ? i + 2 * U : i);  // (a re-read where nothing follows)
+#pragma unroll
+            for (int u = 0; u < U; ++u) vector(gb[u], tb[u], true);
+        }
+    }
+#pragma unroll 1
+    for (; i * kBlock < c.nvec; ++i) {                        // the last one perhaps in some lanes only
+        const uint32_t v = i * kBlock + tid;
+        u32x4 gv, tv;
+        c.load(min(v, c.nvec - 1), gv, tv);
+        vector(gv, tv, v < c.nvec);
+    }
+#pragma unroll 1
+    for (uint32_t e = c.nvec * VEC; e < c.len; e += kBlock) { // fewer than VEC elements
+        const uint32_t q = min(e + tid, c.len - 1);
+        row(load_elem<DG>(c.g, q), load_elem<DT>(c.t, q), e + tid < c.len);
+    }
+    if (qn != 0) work(qn);
+
+    // the wave's last, partly filled segment
+    const uint32_t keys = wl.nseg * kTopkSeg + wl.n;
+    if (wl.n != 0) wl.flush(P, sh.list[wave], dir, wave, wl.n);
+    if (lane == 0) {
+        dir.keys[wave] = keys;
+        if (wl.lost) P.ovf[pair] = 1;
+        sh.cnt[wave][0] = bad;
+        sh.cnt[wave][1] = na;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        uint32_t n = 0;
+        for (int w = 0; w < kWaves; ++w) n += sh.cnt[w][tid];
+        if (n) atomicAdd((unsigned long long *)&P.counts[2 * pair + tid], (unsigned long long)n);
+    }
+    if (tid >= 64 && tid < 64 + kSumBins) {
+        const int b = tid - 64;
+        const uint64_t l = sh.xl[b], h = sh.xh[b];
+        if (l | h) {
+            const uint64_t x = l + (h << 32);
+            atomic_add128(P.xsum + ((size_t)pair * kBins0 + base + b) * 2, x, (h >> 32) + (x < l ? 1u : 0u));
+        }
+    }
+    // the table's keys as entries
+    if (table) {
+        for (int q = tid; q < kTable; q += kBlock)
+            if (tab.cnt[q]) atomicAdd(&tab.n, 1u);
+        __syncthreads();
+        if (tid == 0) {
+            unsigned long long base = 0;
+            uint32_t ok = 1;
+            if (tab.n > 0) {
+                base = atomicAdd(&P.fill[0], (unsigned long long)tab.n);
+                ok = base + tab.n <= P.cap[0];
+            }
+            if (!ok) P.ovf[pair] = 1;
+            tab.base = base;
+            tab.ok = ok;
+            dir.tbase = base;
+            dir.tn = ok ? tab.n : 0u;
+        }
+        __syncthreads();
+        if (tab.ok)
+            for (int q = tid; q < kTable; q += kBlock)
+                if (tab.cnt[q]) P.ents[tab.base + atomicAdd(&tab.pos, 1u)] = TopkEntry{tab.key[q], tab.cnt[q], 0};
+    } else if (tid == 0) {
+        dir.tn = 0;
+    }
+}
+
+// ---- resolve -----------------------------------------------------------------------
+constexpr int kCache = 4096;                    // gathered keys kept in LDS after the first pass over them
+struct ResolveShared {
+    unsigned long long h[kRelBins];
+    uint64_t ckey[kCache];
+    uint64_t ccnt[kCache];
+    uint64_t lkey[kList];
+    uint64_t lcnt[kList];
+    Sel sel;
+    double red[kBigWaves];
+    uint32_t ncache, nlist;
+    uint64_t T, need;
+};
+
+// Calls f(key, count) for the pair's gathered keys: sixteen lanes per group of
+// four chunks, whose headers and then whose entries are in flight together.
+template <typename F>
+__device__ __forceinline__ void for_each_gathered(const TopkParams &P, const SigDesc &d, F &&f) {
+    constexpr int LPC = 16, U = 4, G = kBig / LPC;
+    const int sub = threadIdx.x & (LPC - 1);
+    for (int c0 = threadIdx.x / LPC; c0 < d.nchunks; c0 += U * G) {
+        const TopkDir *dir[U];
+        uint32_t tn[U], nk[U][kWaves], most = 0, single = 0;
+        uint64_t tbase[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            dir[u] = P.dir + d.first_chunk + min(c0 + u * G, d.nchunks - 1);
+            tbase[u] = dir[u]->tbase;
+            tn[u] = dir[u]->tn;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) nk[u][w] = dir[u]->keys[w];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool on = c0 + u * G < d.nchunks;
+            tn[u] = on ? tn[u] : 0u;
+            most = max(most, tn[u]);
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                nk[u][w] = on ? nk[u][w] : 0u;
+                single |= nk[u][w];
+            }
+        }
+        for (uint32_t i = sub; i < most; i += LPC) {
+            TopkEntry e[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i < tn[u]) e[u] = P.ents[tbase[u] + i];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i < tn[u]) f(e[u].key, (uint64_t)e[u].count);
+        }
+        if (single == 0) continue;
+#pragma unroll 1
+        for (int u = 0; u < U; ++u) {
+            const TopkDir *r = P.dir + d.first_chunk + c0 + u * G;
+            if (c0 + u * G >= d.nchunks) break;
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t n = r->keys[w];
+                for (uint32_t i = sub; i < n; i += U * LPC) {
+                    uint64_t k[U];
+#pragma unroll
+                    for (int v = 0; v < U; ++v) {
+                        const uint32_t q = min(i + v * LPC, n - 1);
+                        k[v] = P.pool[(uint64_t)r->seg[w][q / kTopkSeg] * kTopkSeg + q % kTopkSeg];
+                    }
+#pragma unroll
+                    for (int v = 0; v < U; ++v)
+                        if (i + v * LPC < n) f(k[v], uint64_t(1));
                 }
             }
         }
-        if (hist1) {
-#pragma unroll
-            for (int j = 0; j < V; ++j)
-                if (in[j]) atomicAdd(&h[digit_of(key[j], 1)], 1u);
-        }
-        if (samp) {
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                nv += ok[j] ? 1u : 0u;
-                na += (ok[j] && key[j] >= ghi) ? 1u : 0u;
-            }
-        }
-    });
-    if (samp) {
-        // lane counts (at most 2^10 each) summed over the wave
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            nv += __shfl_xor(nv, o);
-            na += __shfl_xor(na, o);
-        }
-        if ((threadIdx.x & 63) == 0) {
-            atomicAdd((unsigned long long *)&P.counts[2 * pair], (unsigned long long)nv);
-            atomicAdd((unsigned long long *)&P.counts[2 * pair + 1], (unsigned long long)na);
-        }
     }
-    const double bs = block_sum(s, red);
-    if (threadIdx.x == 0) P.part_a[gchunk] = bs;
-    if (!active) return;
-    __syncthreads();
-    if (hist1) {
-        uint64_t *H = P.hist + (size_t)pair * kTopkBins;
-        if (tab.full) {
-            for (int i = threadIdx.x; i < kTable; i += kBlock)
-                if (tab.cnt[i]) atomicAdd(&h[digit_of(tab.key[i], 1)], tab.cnt[i]);
-            flush_hist(h, kTopkBins, H);
-        } else {
-            for (int i = threadIdx.x; i < kTable; i += kBlock)
-                if (tab.cnt[i])
-                    atomicAdd((unsigned long long *)&H[digit_of(tab.key[i], 1)], (unsigned long long)tab.cnt[i]);
-        }
-    }
-    table_flush(tab, P, 0, pair, st.round, win);
-    __syncthreads();
 }
 
-// pass C (pairs whose binade did not fit): exact sum of their errors in D0
-// above bin D1 and gather of bin (D0, D1)
-template <int DG, int DT>
-__device__ __forceinline__ void passC_chunk(const TopkParams &P, int64_t gchunk, Table &tab) {
-    const int pair = P.chunk_pair[gchunk];
+__global__ void __launch_bounds__(kBig) topk_resolve(TopkParams P) {
+    __shared__ ResolveShared sh;
+    const int pair = blockIdx.x, tid = threadIdx.x;
     const TopkState st = P.state[pair];
-    if (!(st.status == kTopkActive && st.level == 1 && P.ovf[2 * pair] != 0)) return;
-    const SigDesc d = P.descs[pair];
-    table_init(tab);
-    __syncthreads();
-    const uint64_t b1 = st.key >> digit_shift(1);           // binade and digit 1 of the boundary
-    const int d0 = st.d0;
-    uint64_t x = 0;
-    for_each_error<DG, DT>(d, gchunk - d.first_chunk, [&](uint64_t key, double) {
-        const uint64_t k1 = key >> digit_shift(1);
-        if ((k1 >> 13) == (b1 >> 13) && k1 > b1) x += signif(key, d0);
-        const bool in = k1 == b1;
-        const bool counted = in && table_count(tab, key);
-        spill_entry(in && !counted, key, P, pair, st.round);
-    });
-    block_add128(x, xsum_of(P, pair, d0));
-    tab.full = 0;                                            // keys without a slot went out as entries
-    table_flush(tab, P, 1, pair, st.round, false);
-    __syncthreads();
-}
-
-// pass T_L (pairs whose bin (D0, D1) did not fit either): histogram of digit
-// L (L <= 4) among the errors on the level L-1 prefix, and (L >= 3) the
-// exact sum of the errors on the level L-2 prefix above digit D_{L-1}
-template <int DG, int DT>
-__device__ __forceinline__ void passT_chunk(const TopkParams &P, int64_t gchunk, uint32_t *h) {
-    const int L = P.level;
-    const int pair = P.chunk_pair[gchunk];
-    const TopkState st = P.state[pair];
-    const bool want = L <= kTopkLevels - 1 ? (st.status == kTopkActive && st.level == L - 1) : st.level == L - 1;
-    if (!(want && P.ovf[2 * pair] != 0 && P.ovf[2 * pair + 1] != 0)) return;
-    const SigDesc d = P.descs[pair];
-    const bool hist = L <= kTopkLevels - 1;
-    const bool sum = L >= 3;
-    if (hist) {
-        for (int b = threadIdx.x; b < kTopkBins; b += kBlock) h[b] = 0;
-        __syncthreads();
-    }
-    const int sh = digit_shift(hist ? L - 1 : 0);
-    const uint64_t ph = st.key >> sh;
-    const int sx = digit_shift(sum ? L - 2 : 0);
-    const uint64_t px = st.key >> sx;
-    const uint32_t dl = digit_of(st.key, sum ? L - 1 : 0);
-    const int d0 = st.d0;
-    uint64_t x = 0;
-    for_each_error<DG, DT>(d, gchunk - d.first_chunk, [&](uint64_t key, double) {
-        if (hist && (key >> sh) == ph) atomicAdd(&h[digit_of(key, L)], 1u);
-        if (sum && (key >> sx) == px && digit_of(key, L - 1) > dl) x += signif(key, d0);
-    });
-    if (sum) block_add128(x, xsum_of(P, pair, d0));
-    if (hist) flush_hist(h, kTopkBins, P.hist + (size_t)pair * kTopkBins);
-    __syncthreads();
-}
-
-template <int DG, int DT, int OP>
-__global__ void __launch_bounds__(kBlock) topk_scan(TopkParams P) {
-    __shared__ uint32_t h[kTopkBins];
-    __shared__ double red[kWaves];
-    if constexpr (OP == kPass1) {
-        if (P.round == 0) {
-            pass1_chunk<DG, DT>(P, P.chunk_base + blockIdx.x, h);
-        } else {
-            if (P.ovf[2 * P.count + 2] == 0) return;         // every window fitted
-            for (int64_t c = blockIdx.x; c < P.kind_chunks; c += gridDim.x) {
-                pass1_chunk<DG, DT>(P, P.chunk_base + c, h);
-                __syncthreads();
-            }
+    if (st.status == kTopkDone) return;
+    const SigDesc d = desc_of(P, pair);
+    uint64_t *xs = P.xsum + (size_t)pair * 2 * kBins0;
+    // leaves the pair to the digit passes
+    auto open = [&]() {
+        for (int i = tid; i < 2 * kBins0; i += kBig) {
+            P.hist[(size_t)pair * kTopkHist + i] = 0;
+            xs[i] = 0;
         }
-    } else if constexpr (OP == kPassA) {
-        __shared__ Table tab;
-        if (P.round == 0) {
-            passA_chunk<DG, DT>(P, P.chunk_base + blockIdx.x, h, tab, red);
-        } else {
-            if (P.ovf[2 * P.count + 2] == 0) return;         // every window fitted
-            for (int64_t c = blockIdx.x; c < P.kind_chunks; c += gridDim.x)
-                passA_chunk<DG, DT>(P, P.chunk_base + c, h, tab, red);
+        if (tid == 0) {
+            P.state[pair].status = kTopkOpen;
+            atomicAdd(P.open, 1u);
         }
-    } else if constexpr (OP == kPassC) {
-        __shared__ Table tab;
-        if (P.ovf[2 * P.count] == 0) return;                 // every binade fitted
-        for (int64_t c = blockIdx.x; c < P.kind_chunks; c += gridDim.x) passC_chunk<DG, DT>(P, P.chunk_base + c, tab);
-    } else {
-        if (P.ovf[2 * P.count + 1] == 0) return;             // every bin fitted
-        for (int64_t c = blockIdx.x; c < P.kind_chunks; c += gridDim.x) passT_chunk<DG, DT>(P, P.chunk_base + c, h);
-    }
-}
-
-// ---- selection -----------------------------------------------------------------
-// Loads the pair's histogram (nb bins) into LDS and clears it for the next
-// level; every thread of the block takes part.
-__device__ __forceinline__ void take_hist(uint64_t *H, int nb, uint64_t *hs, uint64_t *ssum) {
-    const int seg = nb / kBlock;
-    for (int b = threadIdx.x; b < nb; b += kBlock) {
-        hs[b] = H[b];
-        H[b] = 0;
-    }
-    __syncthreads();
-    const int top = nb - (int)threadIdx.x * seg;              // thread t: bins [top - seg, top)
-    uint64_t x = 0;
-    for (int b = top - 1; b >= top - seg; --b) x += hs[b];
-    ssum[threadIdx.x] = x;
-    __syncthreads();
-}
-
-// The bin holding the need-th largest counted error (thread 0): walks the
-// segments, then the bins, from the top; acc receives the count above it.
-__device__ __forceinline__ int walk_hist(const uint64_t *hs, const uint64_t *ssum, int nb, uint64_t need,
-                                         uint64_t &acc) {
-    const int seg = nb / kBlock;
-    acc = 0;
-    int t = 0;
-    while (t < kBlock - 1 && acc + ssum[t] < need) acc += ssum[t++];
-    int b = nb - t * seg - 1;
-    while (b > nb - (t + 1) * seg && acc + hs[b] < need) acc += hs[b--];
-    return b;
-}
-
-// One block per pair: the bin of the level-L histogram holding the need-th
-// largest remaining error.
-__global__ void __launch_bounds__(kBlock) topk_select(TopkParams P) {
-    const int pair = blockIdx.x;
-    const int L = P.level;
-    TopkState st = P.state[pair];
-    if (L == 0 ? st.level != -1 : !(st.status == kTopkActive && st.level == L - 1)) return;
-    const int nb = L == 0 ? kBins0 : kTopkBins;
-    __shared__ uint64_t hs[kTopkBins];
-    __shared__ uint64_t ssum[kBlock];
-    take_hist(P.hist + (size_t)pair * kTopkBins, nb, hs, ssum);
-    if (threadIdx.x != 0) return;
-    uint64_t need;
-    if (L == 0) {
-        uint64_t nv = 0;
-        for (int t = 0; t < kBlock; ++t) nv += ssum[t];
-        st.n_valid = nv;
-        st.k = (uint64_t)(((unsigned __int128)nv * (uint32_t)P.num + (uint32_t)P.den - 1) / (uint32_t)P.den);
-        st.need = st.k;
-        st.cand = 0;
-        st.key = 0;
-        if (st.k == 0) {
-            st.level = 0;
-            st.status = kTopkDone;
-            st.d0 = 0;
-            P.state[pair] = st;
-            return;
-        }
-        need = st.k;
-    } else {
-        need = st.need;
-    }
-    uint64_t acc;
-    const int b = walk_hist(hs, ssum, nb, need, acc);
-    st.need = need - acc;                     // copies of the boundary bin taken, >= 1
-    st.cand = hs[b];
-    st.key |= (uint64_t)b << digit_shift(L);
-    if (L == 0) {
-        level0_status(st, b, P.descs[pair].tdtype);
-    } else {
-        st.level = L;
-        st.status = L == kTopkLevels - 1 ? kTopkDone : kTopkActive;
-    }
-    P.state[pair] = st;
-}
-
-// One block per pair whose window was gathered: level 0 from the binade
-// histogram of its entries (need counts from the top of the window; for a
-// guess, from pass A's counts, which also confirm it).  A window that did
-// not fit, or a wrong guess, reopens level 0 for a binade pass and a second
-// gathering round.
-__global__ void __launch_bounds__(kBlock) topk_select_window(TopkParams P) {
-    const int pair = blockIdx.x;
-    TopkState st = P.state[pair];
-    if (st.level != -2) return;
-    if (P.ovf[2 * pair] != 0) {
-        if (threadIdx.x == 0) {
-            st.level = -1;
-            st.round = 1;
-            st.wlo = st.whi = 0;
-            st.need = st.cand = 0;
-            st.sampled = 0;
-            P.ovf[2 * pair] = 0;
-            P.state[pair] = st;
-        }
+    };
+    const uint64_t nv = (uint64_t)d.n - P.counts[2 * pair], na = P.counts[2 * pair + 1];
+    const uint64_t k = top_count(nv, P);
+    if (P.ovf[pair] != 0 || (k != 0 && k <= na)) {
+        open();
         return;
     }
-    __shared__ uint64_t hs[kBins0];
-    __shared__ uint64_t ssum[kBlock];
-    take_hist(P.hist + (size_t)pair * kTopkBins, kBins0, hs, ssum);
-    if (threadIdx.x != 0) return;
-    if (st.sampled) {
-        // the pair's counts decide whether the guessed binade holds the
-        // boundary; otherwise level 0 reopens for a binade pass (round 1)
-        const uint64_t nv = P.counts[2 * pair], above = P.counts[2 * pair + 1];
-        uint64_t w = 0;
-        for (int t = 0; t < kBlock; ++t) w += ssum[t];
-        st.n_valid = nv;
-        st.k = (uint64_t)(((unsigned __int128)nv * (uint32_t)P.num + (uint32_t)P.den - 1) / (uint32_t)P.den);
-        if (st.k == 0) {
-            st.level = 0;
-            st.status = kTopkDone;
-            st.d0 = 0;
-            P.state[pair] = st;
-            return;
+    uint64_t T = 0, need = k - na;
+    if (k != 0) {
+        uint64_t lo = st.wlo, hi = st.whi;
+        bool found = lo == hi;                                // nothing gathered: T is 0
+        bool cached = false;                                  // the gathered keys are in LDS
+        auto for_each_key = [&](auto &&f) {
+            if (cached)
+                for (uint32_t i = tid; i < sh.ncache; i += kBig) f(sh.ckey[i], sh.ccnt[i]);
+            else
+                for_each_gathered(P, d, f);
+        };
+        if (tid == 0) sh.ncache = 0;
+        for (bool first = true; !found; first = false) {      // the range shrinks by 2^12 or ends at one key
+            const int bits = 64 - __builtin_clzll((hi - lo - 1) | 1);
+            const int shift = bits > 12 ? bits - 12 : 0;
+            for (int i = tid; i < kRelBins; i += kBig) sh.h[i] = 0;
+            if (tid == 0) sh.nlist = 0;
+            __syncthreads();
+            for_each_key([&](uint64_t key, uint64_t n) {
+                if (key >= lo && key < hi) atomicAdd(&sh.h[(key - lo) >> shift], (unsigned long long)n);
+                if (first) {
+                    const uint32_t q = atomicAdd(&sh.ncache, 1u);
+                    if (q < kCache) {
+                        sh.ckey[q] = key;
+                        sh.ccnt[q] = n;
+                    }
+                }
+            });
+            __syncthreads();
+            cached = sh.ncache <= kCache;
+            Scan<kBig, kRelBins, uint64_t> scan;
+            scan.take(sh.sel, [&](int b) { return (uint64_t)sh.h[b]; });
+            scan.pick(sh.sel, need);
+            if (sh.sel.bin < 0) {                             // T lies below the window
+                if (st.wlo != 1) {
+                    open();
+                    return;
+                }
+                need -= scan.total;                           // every nonzero error is counted: T is 0
+                break;
+            }
+            need -= sh.sel.above;
+            lo += (uint64_t)sh.sel.bin << shift;
+            hi = min(hi, lo + (uint64_t(1) << shift));
+            if (shift == 0) {
+                T = lo;
+                break;
+            }
+            for_each_key([&](uint64_t key, uint64_t n) {
+                if (key >= lo && key < hi) {
+                    const uint32_t q = atomicAdd(&sh.nlist, 1u);
+                    if (q < kList) {
+                        sh.lkey[q] = key;
+                        sh.lcnt[q] = n;
+                    }
+                }
+            });
+            __syncthreads();
+            const uint32_t m = sh.nlist;
+            if (m <= kList) {
+                // the listed keys' ranks
+                if ((uint32_t)tid < m) {
+                    const uint64_t mykey = sh.lkey[tid];
+                    uint64_t gt = 0, ge = 0;
+                    for (uint32_t q = 0; q < m; ++q) {
+                        const uint64_t n = sh.lcnt[q], o = sh.lkey[q];
+                        gt += o > mykey ? n : 0;
+                        ge += o >= mykey ? n : 0;
+                    }
+                    if (gt < need && need <= ge) {            // every copy writes the same
+                        sh.T = mykey;
+                        sh.need = need - gt;
+                    }
+                }
+                __syncthreads();
+                T = sh.T;
+                need = sh.need;
+                found = true;
+            }
+            __syncthreads();
         }
-        if (st.k <= above || st.k > above + w) {
-            st.level = -1;
-            st.round = 1;
-            st.wlo = st.whi = 0;
-            st.need = st.cand = 0;
-            st.sampled = 0;
-            P.ovf[2 * P.count + 2] = 1;
-            P.state[pair] = st;
-            return;
+        // the gathered keys above T: those of T's binade and the next one in
+        // registers, others straight to the pair's sums
+        const uint64_t b0 = T >> 52;
+        uint64_t xl[2] = {0, 0}, xh[2] = {0, 0};
+        if (st.wlo != st.whi)
+            for_each_key([&](uint64_t key, uint64_t n) {
+                if (key <= T) return;
+                const uint64_t b = key >> 52;
+                const unsigned __int128 v = (unsigned __int128)n * signif(key, (int)b);
+                if (b - b0 < 2) {
+                    const int i = (int)(b - b0);
+                    const uint64_t v0 = i == 0 ? (uint64_t)v : 0, v1 = i == 1 ? (uint64_t)v : 0;
+                    xl[0] += v0;
+                    xh[0] += (i == 0 ? (uint64_t)(v >> 64) : 0) + (xl[0] < v0 ? 1u : 0u);
+                    xl[1] += v1;
+                    xh[1] += (i == 1 ? (uint64_t)(v >> 64) : 0) + (xl[1] < v1 ? 1u : 0u);
+                } else {
+                    atomic_add128(xs + 2 * b, (uint64_t)v, (uint64_t)(v >> 64));
+                }
+            });
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            wave_add128(xl[i], xh[i]);
+            if ((tid & 63) == 0 && b0 + i < (uint64_t)kBins0) atomic_add128(xs + 2 * (b0 + i), xl[i], xh[i]);
         }
-        st.need = st.k - above;
     }
-    uint64_t acc;
-    const int b = walk_hist(hs, ssum, kBins0, st.need, acc);
-    st.need -= acc;
-    st.cand = hs[b];
-    st.key = (uint64_t)b << 52;
-    level0_status(st, b, P.descs[pair].tdtype);
-    P.state[pair] = st;
-}
-
-// ---- rounds on the entries -------------------------------------------------------
-// Region 0 holds the binade and window gathers of pass A, region 1 the bin
-// gathers of pass C; an entry counts for its pair when the pair takes that
-// route and the entry comes from the pair's gathering round.
-template <typename F>
-__device__ __forceinline__ void for_each_entry(const TopkParams &P, F &&f) {
-    for (int r = 0; r < 2; ++r) {
-        const unsigned long long fill = P.fill[r];
-        const uint64_t n = fill < P.cap[r] ? fill : P.cap[r];
-        const TopkEntry *E = P.ents + (r ? P.cap[0] : 0);
-        for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock) {
-            const TopkEntry e = E[i];
-            if (e.pair < 0) continue;
-            const int pair = (int)((uint32_t)e.pair & kPairMask);
-            if (pair >= P.count) continue;
-            if (pair_mode(P, pair) != (r ? kModeC : kModeA)) continue;
-            const TopkState &st = P.state[pair];
-            if ((int)((uint32_t)e.pair >> 30) != st.round) continue;
-            f(e, pair, st);
-        }
-    }
-}
-
-// Level L: weighted histogram of digit L over the entries on the pair's
-// level L-1 prefix.  Level 0 serves the window pairs (every entry is in the
-// window), level 1 the window pairs only (the others got their digit-1
-// histogram from pass A), levels 2-4 every pair on entries.
-__global__ void __launch_bounds__(kBlock) topk_ent_hist(TopkParams P) {
-    const int L = P.level;
-    for_each_entry(P, [&](const TopkEntry &e, int pair, const TopkState &st) {
-        if (L == 0) {
-            if (st.level != -2) return;
-        } else {
-            if (!(st.status == kTopkActive && st.level == L - 1)) return;
-            if (L == 1 && !is_window(st)) return;
-            const int sh = digit_shift(L - 1);
-            if ((e.key >> sh) != (st.key >> sh)) return;
-        }
-        atomicAdd((unsigned long long *)&P.hist[(size_t)pair * kTopkBins + digit_of(e.key, L)],
-                  (unsigned long long)e.count);
-    });
-}
-
-// Exact sums of the entries above the fixed boundary, per binade.
-__global__ void __launch_bounds__(kBlock) topk_ent_sum(TopkParams P) {
-    for_each_entry(P, [&](const TopkEntry &e, int pair, const TopkState &st) {
-        if (st.level != kTopkLevels - 1 || e.key <= st.key) return;
-        const int b = (int)(e.key >> 52);
-        const unsigned __int128 v = (unsigned __int128)e.count * signif(e.key, b);
-        atomic_add128(xsum_of(P, pair, b), (uint64_t)v, (uint64_t)(v >> 64));
-    });
-}
-
-// ---- records -------------------------------------------------------------------
-// Fixed-order sum over the pair's chunk partials (thread t sums chunks t,
-// t + 256, ... in order; then butterflies and waves in order).
-__device__ __forceinline__ double chunk_sum(const double *part, int64_t first, int64_t n, double *red) {
-    double s = 0.0;
-    for (int64_t c = threadIdx.x; c < n; c += kBlock) s += part[first + c];
-    const double r = block_sum(s, red);
+    __builtin_amdgcn_s_waitcnt(0);                            // the wave's atomics are done
     __syncthreads();
-    return r;
+    const double sum = binade_sums(xs, need, T, (int)(T >> 52), sh.red);
+    if (tid == 0) {
+        write_record(P.outs + pair, nv, k, need, T, sum);
+        P.state[pair].status = kTopkDone;
+    }
 }
 
-// The binary64 value of an exact significand sum of binade b (the boundary's
-// binade with need copies of T added).
-__device__ __forceinline__ double binade_value(const TopkParams &P, int pair, const TopkState &st, int b) {
-    const uint64_t *xp = xsum_of(P, pair, b);
-    unsigned __int128 x = ((unsigned __int128)xp[1] << 64) | xp[0];
-    if (b == st.d0) x += (unsigned __int128)st.need * signif(st.key, st.d0);
-    if (x == 0) return 0.0;
-    const double xd = (double)(uint64_t)(x >> 64) * 0x1p64 + (double)(uint64_t)x;
-    return __builtin_ldexp(xd, (b != 0 ? b : 1) - 1075);
+// ---- digit passes ------------------------------------------------------------------
+// Pass q of an open pair first selects digit q - 1 from its histogram (every
+// block for itself; the block of the pair's first chunk writes the level down
+// and clears the next pass's histogram: three are used in turn), then
+// counts digit q of the errors on the prefix (q < 6) and sums: pass 1 the
+// errors above the binade D0 just selected, a later pass those of D0 on the
+// prefix before it above digit q - 1.
+struct DigitShared {
+    uint32_t h[kBins0];
+    unsigned long long xl[kBins0], xh[kBins0];   // pass 1: significand sums per binade, as in the gather
+    Sel sel;
+};
+__device__ __forceinline__ uint64_t *hist_of(const TopkParams &P, int pair, int level) {
+    return P.hist + (size_t)pair * kTopkHist + (size_t)(level % 3) * kBins0;
 }
 
-__global__ void __launch_bounds__(kBlock) topk_finalize(TopkParams P) {
-    __shared__ double red[kWaves];
-    __shared__ double xb[kBins0];
-    const int pair = blockIdx.x;
-    const SigDesc d = P.descs[pair];
-    const TopkState st = P.state[pair];
-    const double sa = chunk_sum(P.part_a, d.first_chunk, d.nchunks, red);
-    // a window's binades above D0: their exact sums converted in parallel,
-    // added in a fixed order (from the top) below
-    const bool ordinary = st.k != 0 && st.d0 != kBins0 - 1 && !(st.d0 == 0 && st.level == 0);
-    const int top = ordinary && is_window(st) ? (int)((st.whi - 1) >> 52) : st.d0;
-    if (ordinary && top > st.d0) {
-        for (int b = st.d0 + threadIdx.x; b <= top; b += kBlock) xb[b] = binade_value(P, pair, st, b);
+template <int DG, int DT>
+__device__ __forceinline__ void digit_pass(const TopkParams &P, int64_t gchunk, DigitShared &sh) {
+    const int q = P.level, tid = threadIdx.x;
+    const int pair = pair_of(P, gchunk);
+    if (P.state[pair].status != kTopkOpen) return;
+    const SigDesc d = desc_of(P, pair);
+    const bool first = gchunk == d.first_chunk;
+    TopkLevel lv{0, 0, 0, 0};
+    if (q >= 1) {
+        // (levels below 0 start from nothing; a boundary fixed early leaves nothing to select)
+        if (q >= 2) {
+            const TopkLevel l0 = P.levels[(size_t)pair * kTopkLevels];
+            const int d0 = (int)(l0.key >> 52);
+            if (l0.k == 0 || d0 == kBins0 - 1 || (d0 == 0 && d.tdtype != PEAT_F64)) return;
+            lv = P.levels[(size_t)pair * kTopkLevels + q - 2];
+        }
+        const uint64_t *H = hist_of(P, pair, q - 1);
+        uint64_t need = lv.need;
+        Scan<kBlock, kBins0, uint64_t> scan;
+        scan.take(sh.sel, [&](int b) { return H[b]; });
+        if (q == 1) {
+            lv.n_valid = scan.total;
+            lv.k = need = top_count(lv.n_valid, P);
+        }
+        if (lv.k != 0) {
+            scan.pick(sh.sel, need);
+            lv.key |= (uint64_t)sh.sel.bin << digit_shift(q - 1);
+            lv.need = need - sh.sel.above;
+        }
+        __syncthreads();
+        if (first) {
+            if (tid == 0) P.levels[(size_t)pair * kTopkLevels + q - 1] = lv;
+            uint64_t *N = hist_of(P, pair, q + 1);
+            for (int b = tid; b < kBins0; b += kBlock) N[b] = 0;
+        }
+    }
+    const int d0 = (int)(lv.key >> 52);
+    if (q == 1 && (lv.k == 0 || d0 == kBins0 - 1)) return;
+    const bool fixed = q >= 1 && d0 == 0 && d.tdtype != PEAT_F64;          // the k-th largest error is 0
+    const bool hist = q < kTopkLevels && !fixed;
+    const bool sum = q >= 2;
+    for (int b = tid; b < kBins0; b += kBlock) {
+        sh.h[b] = 0;
+        if (q == 1) sh.xl[b] = sh.xh[b] = 0;
+    }
+    __syncthreads();
+    const int sp = digit_shift(q >= 1 ? q - 1 : 0), sx = digit_shift(q >= 2 ? q - 2 : 0);
+    const uint64_t pre = lv.key >> sp, prex = lv.key >> sx;
+    const uint64_t end = (uint64_t)(d0 + 1) << 52;
+    uint64_t x = 0;
+    for_each_error<DG, DT>(d, gchunk - d.first_chunk, [&](uint64_t key, double) {
+        if (q == 1 && key >= end) {
+            const int b = (int)(key >> 52);
+            const uint64_t v = signif(key, b);
+            atomicAdd(&sh.xl[b], (unsigned long long)(uint32_t)v);
+            atomicAdd(&sh.xh[b], (unsigned long long)(v >> 32));
+        }
+        if (hist && (q == 0 || (key >> sp) == pre)) atomicAdd(&sh.h[digit_of(key, q)], 1u);
+        if (sum && (key >> sx) == prex && (key >> sp) > pre) x += signif(key, d0);
+    });
+    uint64_t *xs = P.xsum + (size_t)pair * 2 * kBins0;
+    if (sum) block_add128(x, xs + 2 * d0);
+    __syncthreads();
+    if (q == 1)
+        for (int b = tid; b < kBins0; b += kBlock) {
+            const uint64_t l = sh.xl[b], h = sh.xh[b];
+            if (!(l | h)) continue;
+            const uint64_t v = l + (h << 32);
+            atomic_add128(xs + 2 * b, v, (h >> 32) + (v < l ? 1u : 0u));
+        }
+    if (hist) {
+        uint64_t *H = hist_of(P, pair, q);
+        for (int b = tid; b < kBins0; b += kBlock)
+            if (sh.h[b]) atomicAdd((unsigned long long *)&H[b], (unsigned long long)sh.h[b]);
+    }
+}
+
+template <int DG, int DT>
+__global__ void __launch_bounds__(kBlock) topk_digit(TopkParams P) {
+    __shared__ DigitShared sh;
+    if (*P.open == 0) return;                                 // no pair left
+    for (int64_t c = blockIdx.x; c < P.kind_chunks; c += gridDim.x) {
+        digit_pass<DG, DT>(P, P.chunk_base + c, sh);
         __syncthreads();
     }
-    if (threadIdx.x != 0) return;
-    const double qnan = opaque_double(0x7FF80000u, 0u);
-    const double inf = opaque_double(0x7FF00000u, 0u);
-    peat_topk_t o;
-    o.n_valid = (int64_t)st.n_valid;
-    o.k = (int64_t)st.k;
-    if (st.k == 0) {
-        o.count_above = 0;
-        o.kth_value = qnan;
-        o.sum_topk = 0.0;
-        o.mean_topk = qnan;
-    } else if (st.d0 == kBins0 - 1) {                 // the k-th largest error is infinite
-        o.count_above = (int64_t)(st.k - st.need);
-        o.kth_value = inf;
-        o.sum_topk = inf;
-        o.mean_topk = inf;
-    } else if (!ordinary) {                           // the k-th largest error is 0
-        o.count_above = (int64_t)(st.k - st.need);
-        o.kth_value = 0.0;
-        o.sum_topk = sa;
-        o.mean_topk = sa / (double)st.k;
-    } else {
-        // exact sums: binade D0 (everything above T, then need copies of T)
-        // and, for a window, each binade above it
-        double sc;
-        if (top > st.d0) {
-            sc = 0.0;
-            for (int b = top; b >= st.d0; --b) sc += xb[b];
-        } else {
-            sc = binade_value(P, pair, st, st.d0);
-        }
-        o.count_above = (int64_t)(st.k - st.need);
-        o.kth_value = __longlong_as_double((long long)st.key);
-        o.sum_topk = sa + sc;
-        o.mean_topk = o.sum_topk / (double)st.k;
-    }
-    P.outs[pair] = o;
 }
 
-__global__ void __launch_bounds__(kBlock) topk_zero(uint64_t *p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) p[i] = 0;
+__global__ void __launch_bounds__(kBig) topk_finish(TopkParams P) {
+    __shared__ double red[kBigWaves];
+    const int pair = blockIdx.x;
+    if (*P.open == 0 || P.state[pair].status != kTopkOpen) return;
+    const SigDesc d = desc_of(P, pair);
+    const TopkLevel *L = P.levels + (size_t)pair * kTopkLevels;
+    const int d0 = (int)(L[0].key >> 52);
+    const bool early = L[0].k == 0 || d0 == kBins0 - 1 || (d0 == 0 && d.tdtype != PEAT_F64);
+    const TopkLevel lv = L[early ? 0 : kTopkLevels - 1];
+    const double sum = binade_sums(P.xsum + (size_t)pair * 2 * kBins0, lv.need, lv.key, d0, red);
+    if (threadIdx.x == 0) write_record(P.outs + pair, L[0].n_valid, L[0].k, lv.need, lv.key, sum);
 }
 
 // ---- launches ---------------------------------------------------------------------
-template <int DG, int DT, int OP>
-void launch_one(const TopkParams &q, hipStream_t s) {
+template <int DG, int DT>
+void launch_one(const TopkParams &q, bool gather, hipStream_t s) {
     const int64_t n = q.kind_chunks;
-    const bool full = (OP == kPass1 || OP == kPassA) && q.round == 0;   // one chunk per block
-    const int64_t grid = full ? n : (n < kScanGrid ? n : kScanGrid);
-    hipLaunchKernelGGL((topk_scan<DG, DT, OP>), dim3((unsigned)grid), dim3(kBlock), 0, s, q);
+    if (gather)
+        hipLaunchKernelGGL((topk_gather<DG, DT>), dim3((unsigned)n), dim3(kBlock), 0, s, q);
+    else
+        hipLaunchKernelGGL((topk_digit<DG, DT>), dim3((unsigned)(n < kScanGrid ? n : kScanGrid)), dim3(kBlock), 0, s, q);
 }
 
-template <int OP>
-hipError_t launch_scan(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s) {
+hipError_t launch_kinds(const TopkParams &p, const int64_t range[kKinds + 1], bool gather, hipStream_t s) {
     static_assert(kKindTypes[3][1] == PEAT_F64 && kKindTypes[9][0] == PEAT_BF16, "kind table order");
     for (int kind = 0; kind < kKinds; ++kind) {
         const int64_t n = range[kind + 1] - range[kind];
@@ -1104,110 +1200,49 @@ hipError_t launch_scan(const TopkParams &p, const int64_t range[kKinds + 1], hip
         q.chunk_base = range[kind];
         q.kind_chunks = n;
         switch (kind) {
-            case 0: launch_one<PEAT_F32, PEAT_F32, OP>(q, s); break;
-            case 1: launch_one<PEAT_F16, PEAT_F16, OP>(q, s); break;
-            case 2: launch_one<PEAT_BF16, PEAT_BF16, OP>(q, s); break;
-            case 3: launch_one<PEAT_F32, PEAT_F64, OP>(q, s); break;
-            case 4: launch_one<PEAT_F32, PEAT_F16, OP>(q, s); break;
-            case 5: launch_one<PEAT_F32, PEAT_BF16, OP>(q, s); break;
-            case 6: launch_one<PEAT_F16, PEAT_F32, OP>(q, s); break;
-            case 7: launch_one<PEAT_BF16, PEAT_F32, OP>(q, s); break;
-            case 8: launch_one<PEAT_F16, PEAT_F64, OP>(q, s); break;
-            default: launch_one<PEAT_BF16, PEAT_F64, OP>(q, s); break;
+            case 0: launch_one<PEAT_F32, PEAT_F32>(q, gather, s); break;
+            case 1: launch_one<PEAT_F16, PEAT_F16>(q, gather, s); break;
+            case 2: launch_one<PEAT_BF16, PEAT_BF16>(q, gather, s); break;
+            case 3: launch_one<PEAT_F32, PEAT_F64>(q, gather, s); break;
+            case 4: launch_one<PEAT_F32, PEAT_F16>(q, gather, s); break;
+            case 5: launch_one<PEAT_F32, PEAT_BF16>(q, gather, s); break;
+            case 6: launch_one<PEAT_F16, PEAT_F32>(q, gather, s); break;
+            case 7: launch_one<PEAT_BF16, PEAT_F32>(q, gather, s); break;
+            case 8: launch_one<PEAT_F16, PEAT_F64>(q, gather, s); break;
+            default: launch_one<PEAT_BF16, PEAT_F64>(q, gather, s); break;
         }
-        hipError_t e = hipGetLastError();
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-// The sample kernel of every kind present (one block per pair; blocks of
-// other kinds' pairs return at once).
-hipError_t launch_sample(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s) {
-    for (int kind = 0; kind < kKinds; ++kind) {
-        if (range[kind + 1] - range[kind] <= 0) continue;
-        const dim3 grid((unsigned)p.count), block(kBlock);
-        switch (kind) {
-            case 0: hipLaunchKernelGGL((topk_sample<PEAT_F32, PEAT_F32>), grid, block, 0, s, p); break;
-            case 1: hipLaunchKernelGGL((topk_sample<PEAT_F16, PEAT_F16>), grid, block, 0, s, p); break;
-            case 2: hipLaunchKernelGGL((topk_sample<PEAT_BF16, PEAT_BF16>), grid, block, 0, s, p); break;
-            case 3: hipLaunchKernelGGL((topk_sample<PEAT_F32, PEAT_F64>), grid, block, 0, s, p); break;
-            case 4: hipLaunchKernelGGL((topk_sample<PEAT_F32, PEAT_F16>), grid, block, 0, s, p); break;
-            case 5: hipLaunchKernelGGL((topk_sample<PEAT_F32, PEAT_BF16>), grid, block, 0, s, p); break;
-            case 6: hipLaunchKernelGGL((topk_sample<PEAT_F16, PEAT_F32>), grid, block, 0, s, p); break;
-            case 7: hipLaunchKernelGGL((topk_sample<PEAT_BF16, PEAT_F32>), grid, block, 0, s, p); break;
-            case 8: hipLaunchKernelGGL((topk_sample<PEAT_F16, PEAT_F64>), grid, block, 0, s, p); break;
-            default: hipLaunchKernelGGL((topk_sample<PEAT_BF16, PEAT_F64>), grid, block, 0, s, p); break;
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-hipError_t launch_select(const TopkParams &p, int level, hipStream_t s) {
-    TopkParams q = p;
-    q.level = level;
-    hipLaunchKernelGGL(topk_select, dim3((unsigned)p.count), dim3(kBlock), 0, s, q);
-    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_topk_level0(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s) {
+static_assert(kSmallN == kTopkSmall, "pairs that the start kernel settles");
+
+hipError_t launch_topk_start(const TopkParams &p, hipStream_t s) {
     if (p.count <= 0) return hipSuccess;
-    hipError_t e;
-    auto zero = [&](uint64_t *x, int64_t n) {
-        const int64_t zb = (n + kBlock - 1) / kBlock;
-        hipLaunchKernelGGL(topk_zero, dim3((unsigned)(zb < 65536 ? zb : 65536)), dim3(kBlock), 0, s, x, n);
-    };
-    zero(p.hist, (int64_t)kTopkBins * p.count);
-    zero(p.xsum, (int64_t)2 * kBins0 * p.count);
-    hipLaunchKernelGGL(topk_init, dim3((unsigned)((p.count + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_sample(p, range, s)) != hipSuccess) return e;
-    TopkParams q = p;
-    q.round = 0;
-    if ((e = launch_scan<kPass1>(q, range, s)) != hipSuccess) return e;
-    return launch_select(q, 0, s);
+    hipLaunchKernelGGL(topk_start, dim3((unsigned)p.count), dim3(kBig), 0, s, p);
+    return hipGetLastError();
 }
 
-hipError_t launch_topk_rest(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s) {
+hipError_t launch_topk_gather(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s) {
     if (p.count <= 0) return hipSuccess;
-    hipError_t e;
+    const hipError_t e = launch_kinds(p, range, true, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(topk_resolve, dim3((unsigned)p.count), dim3(kBig), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_topk_digits(const TopkParams &p, const int64_t range[kKinds + 1], hipStream_t s) {
+    if (p.count <= 0) return hipSuccess;
     TopkParams q = p;
-    auto ent_hist = [&](int L) {
-        q.level = L;
-        hipLaunchKernelGGL(topk_ent_hist, dim3(kEntGrid), dim3(kBlock), 0, s, q);
-        return hipGetLastError();
-    };
-    // round 0: binade D0 or the window; level 0 of the windows from their entries
-    q.round = 0;
-    if ((e = launch_scan<kPassA>(q, range, s)) != hipSuccess) return e;
-    if ((e = ent_hist(0)) != hipSuccess) return e;
-    hipLaunchKernelGGL(topk_select_window, dim3((unsigned)p.count), dim3(kBlock), 0, s, q);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // round 1: windows that did not fit and wrong guesses take the binade pass and are gathered again
-    q.round = 1;
-    if ((e = launch_scan<kPass1>(q, range, s)) != hipSuccess) return e;
-    if ((e = launch_select(q, 0, s)) != hipSuccess) return e;
-    if ((e = launch_scan<kPassA>(q, range, s)) != hipSuccess) return e;
-    q.round = 0;
-    // level 1 (the windows from their entries), the bin gathers, levels 2-4
-    if ((e = ent_hist(1)) != hipSuccess) return e;
-    if ((e = launch_select(q, 1, s)) != hipSuccess) return e;
-    if ((e = launch_scan<kPassC>(q, range, s)) != hipSuccess) return e;
-    for (int L = 2; L <= kTopkLevels - 1; ++L) {
-        if ((e = ent_hist(L)) != hipSuccess) return e;
-        q.level = L;
-        if ((e = launch_scan<kPassT>(q, range, s)) != hipSuccess) return e;
-        if ((e = launch_select(q, L, s)) != hipSuccess) return e;
+    for (q.level = 0; q.level <= kTopkLevels; ++q.level) {
+        const hipError_t e = launch_kinds(q, range, false, s);
+        if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(topk_ent_sum, dim3(kEntGrid), dim3(kBlock), 0, s, q);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    q.level = kTopkLevels;
-    if ((e = launch_scan<kPassT>(q, range, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(topk_finalize, dim3((unsigned)p.count), dim3(kBlock), 0, s, q);
+    hipLaunchKernelGGL(topk_finish, dim3((unsigned)p.count), dim3(kBig), 0, s, p);
     return hipGetLastError();
 }
 
