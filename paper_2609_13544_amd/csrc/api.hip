@@ -459,6 +459,26 @@ int check_item(const peat_inject_item_t &it, int k) {
     return PEAT_OK;
 }
 
+// Which items' tensors overlap another item's.
+std::vector<char> shared_tensors(const peat_inject_item_t *items, int32_t count) {
+    std::vector<char> shared((size_t)count, 0);
+    std::vector<std::pair<uintptr_t, int>> at;
+    for (int k = 0; k < count; ++k)
+        if (items[k].n > 0) at.push_back({reinterpret_cast<uintptr_t>(items[k].tensor), k});
+    std::sort(at.begin(), at.end());
+    uintptr_t end = 0;
+    int holder = -1;                         // the item whose tensor ends there
+    for (const auto &a : at) {
+        if (a.first < end) shared[a.second] = shared[holder] = 1;
+        const uintptr_t e = a.first + (uintptr_t)items[a.second].n * (uintptr_t)elem_size(items[a.second].dtype);
+        if (e > end) {
+            end = e;
+            holder = a.second;
+        }
+    }
+    return shared;
+}
+
 int inject_core(const peat_inject_item_t *items, int32_t count, int64_t *d_counts,
                 int64_t *host_counts, hipStream_t s) {
     if (count < 0) return fail(PEAT_EINVAL, "count < 0");
@@ -475,7 +495,11 @@ int inject_core(const peat_inject_item_t *items, int32_t count, int64_t *d_count
     Dev &d = *dv;
 
     std::vector<InjDesc> descs((size_t)count);
-    int64_t total = 0;
+    int64_t elems = 0, total = 0;
+    for (int k = 0; k < count; ++k) elems += items[k].n;
+    int seg_log2 = kInjMaxSegLog2;
+    while (seg_log2 > kInjMinSegLog2 && (elems >> seg_log2) < kInjBlocks) --seg_log2;
+    bool lists = false;
     for (int k = 0; k < count; ++k) {
         const peat_inject_item_t &it = items[k];
         InjDesc &q = descs[k];
@@ -487,12 +511,12 @@ int inject_core(const peat_inject_item_t *items, int32_t count, int64_t *d_count
         q.popc = __builtin_popcountll(q.mask);
         q.model = it.model;
         q.src = nullptr;
-        q.reserved = 0;
+        q.list_cap = 0;
         q.all = it.rate >= 1.0;
         // T = floor(rate * 2^64): ldexp is exact and the conversion truncates
         q.T = (q.all || it.rate == 0.0) ? 0 : (uint64_t)std::ldexp(it.rate, 64);
         const bool none = !q.all && q.T == 0;
-        const int64_t nseg = none ? 0 : (it.n + (int64_t(1) << kInjSegLog2) - 1) >> kInjSegLog2;
+        const int64_t nseg = none ? 0 : (it.n + (int64_t(1) << seg_log2) - 1) >> seg_log2;
         q.first_seg = total;
         q.nsegs = (int32_t)nseg;
         total += nseg;
@@ -503,14 +527,30 @@ int inject_core(const peat_inject_item_t *items, int32_t count, int64_t *d_count
     const size_t b_map = align_up(sizeof(int32_t) * (size_t)total);
     const size_t b_seg = align_up(sizeof(uint32_t) * (size_t)total);
     const size_t b_out = host_counts ? align_up(sizeof(int64_t) * count) : 0;
-    // the random-value items read their sources from copies of their tensors
-    // taken before the injection kernel writes anything
+    // The random-value items' sources are read before anything is written: at
+    // a low rate the chosen elements' new values are listed per segment (room
+    // for 40 standard deviations above the mean) and written by a second
+    // kernel; where the lists would take more than half the tensor's bytes the
+    // sources come from a copy of it (6 of 24 f32 [4096, 4096] tensors at 1e-6:
+    // the copies took 163 of 268 us).
+    // (A tensor that another item changes is copied too.)
+    const std::vector<char> shared = shared_tensors(items, count);
     std::vector<size_t> copy_off((size_t)count, 0);
     size_t b_copy = 0;
     for (int k = 0; k < count; ++k) {
         if (descs[k].model != PEAT_MODEL_VALUE || descs[k].nsegs == 0) continue;
         copy_off[k] = b_copy;
-        b_copy += align_up((size_t)items[k].n * (size_t)elem_size(items[k].dtype));
+        const size_t bytes = (size_t)items[k].n * (size_t)elem_size(items[k].dtype);
+        const double mean = std::ldexp(std::min(items[k].rate, 1.0), seg_log2);
+        const double cap = std::ceil(mean + 40.0 * std::sqrt(mean) + 400.0);
+        const double want = cap * sizeof(uint64_t) * descs[k].nsegs;
+        if (!shared[k] && (want <= 0.5 * (double)bytes || want <= 65536.0)) {
+            descs[k].list_cap = (int32_t)cap;
+            lists = true;
+            b_copy += align_up((size_t)want);
+        } else {
+            b_copy += align_up(bytes);
+        }
     }
     const size_t o_copy = b_desc + b_map + b_seg + b_out;
 
@@ -527,7 +567,7 @@ int inject_core(const peat_inject_item_t *items, int32_t count, int64_t *d_count
         for (int32_t c = 0; c < descs[k].nsegs; ++c) hmap[descs[k].first_seg + c] = k;
     HIP_OR_FAIL(hipMemcpyAsync(ws, h, b_desc + sizeof(int32_t) * (size_t)total, hipMemcpyHostToDevice, s));
     for (int k = 0; k < count; ++k)
-        if (descs[k].model == PEAT_MODEL_VALUE && descs[k].nsegs > 0)
+        if (descs[k].model == PEAT_MODEL_VALUE && descs[k].nsegs > 0 && descs[k].list_cap == 0)
             HIP_OR_FAIL(hipMemcpyAsync(const_cast<void *>(descs[k].src), items[k].tensor,
                                        (size_t)items[k].n * (size_t)elem_size(items[k].dtype),
                                        hipMemcpyDeviceToDevice, s));
@@ -538,10 +578,12 @@ int inject_core(const peat_inject_item_t *items, int32_t count, int64_t *d_count
     P.seg_counts = reinterpret_cast<uint32_t *>(ws + b_desc + b_map);
     P.counts = host_counts ? reinterpret_cast<int64_t *>(ws + b_desc + b_map + b_seg) : d_counts;
     P.count = count;
+    P.seg_log2 = seg_log2;
 
     hipEvent_t ev;
     if ((rc = prof_begin(d, s, &ev))) return rc;
     HIP_OR_FAIL(launch_inject(P, total, s));
+    if (lists) HIP_OR_FAIL(launch_inject_apply(P, total, s));
     if ((rc = prof_end(d, s, 2, ev))) return rc;
     if ((rc = prof_begin(d, s, &ev))) return rc;
     HIP_OR_FAIL(launch_inject_sum(P, s));

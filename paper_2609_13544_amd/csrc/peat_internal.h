@@ -17,7 +17,11 @@ constexpr int kHistSlots = PEAT_MAX_BINS + 3;      // zero | under | bins | over
 constexpr uint32_t kNone = 0xFFFFFFFFu;            // "no element" local index
 constexpr int kMinChunkLog2 = 12;                  // 4096 elements: 16 per thread
 constexpr int kMaxChunkLog2 = 18;                  // 262144 elements: 1024 per thread
-constexpr int kInjSegLog2 = 20;                    // injector segment: 2^20 elements
+// Injector segment (one block): 2^20 elements at most, smaller ones until a
+// launch has kInjBlocks blocks (eight per compute unit: one alone leaves each
+// SIMD with a single wave), 2^13 at least (one group of 32 per thread).
+constexpr int kInjMaxSegLog2 = 20, kInjMinSegLog2 = 13;
+constexpr int64_t kInjBlocks = 2048;
 
 // Chunk size of a pair depends on n only, so that a pair's partition (and
 // hence its binary64 summation tree) is the same in single and batched calls.
@@ -124,14 +128,14 @@ struct InjDesc {                 // one per injected tensor (80 bytes)
     uint64_t seed;
     uint64_t T;                  // floor(rate * 2^64) when !all
     uint64_t mask;
-    const void *src;             // PEAT_MODEL_VALUE: copy of x taken before the call
+    const void *src;             // PEAT_MODEL_VALUE: the item's lists, or a copy of x taken before the call
     int64_t first_seg;
     int32_t nsegs;
     int32_t dtype;
     int32_t all;                 // rate >= 1
     int32_t popc;                // popcount(mask)
     int32_t model;               // peat_model_t
-    int32_t reserved;
+    int32_t list_cap;            // PEAT_MODEL_VALUE: entries of a segment's list (0: src is a copy)
 };
 static_assert(sizeof(InjDesc) == 80, "InjDesc layout");
 
@@ -141,6 +145,7 @@ struct InjParams {
     uint32_t *seg_counts;        // flips per segment
     int64_t *counts;             // flips per item (device)
     int32_t count;
+    int32_t seg_log2;
 };
 
 // ---- top-k error mean --------------------------------------------------------
@@ -224,6 +229,7 @@ hipError_t launch_sig_chunks_inject(const SigParams &p, const int64_t range[kKin
 hipError_t launch_sig_finalize(const SigParams &p, hipStream_t s);
 hipError_t launch_inject(const InjParams &p, int64_t total_segs, hipStream_t s);
 hipError_t launch_inject_sum(const InjParams &p, hipStream_t s);
+hipError_t launch_inject_apply(const InjParams &p, int64_t total_segs, hipStream_t s);
 hipError_t launch_corrupt_positions(void *x, int64_t n, int dtype, uint64_t seed, int model, int64_t num_pos,
                                     uint64_t mask, int64_t *d_positions, hipStream_t s);
 hipError_t launch_cast_round(void *x, int64_t n, int to_dtype, hipStream_t s);

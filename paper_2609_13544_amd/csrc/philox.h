@@ -35,6 +35,41 @@ __device__ __forceinline__ void philox(uint64_t c, uint32_t s, uint64_t seed, ui
     out[3] = x3;
 }
 
+// Block number (hi, lo) of stream 0, hi the same for the whole wave: the
+// counter's other half is 0, so the first round has one product and the
+// second one vector product (the other one's operand is uniform).
+__device__ __forceinline__ void philox0(uint32_t lo, uint32_t hi, uint64_t seed, uint32_t out[4]) {
+    uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    const uint64_t a = (uint64_t)kPhiloxM0 * lo;
+    const uint32_t u0 = hi ^ k0;
+    uint32_t x2 = (uint32_t)(a >> 32) ^ k1, x3 = (uint32_t)a;
+    k0 += kPhiloxW0;
+    k1 += kPhiloxW1;
+    const uint64_t b = (uint64_t)kPhiloxM0 * u0, c = (uint64_t)kPhiloxM1 * x2;
+    uint32_t x0 = (uint32_t)(c >> 32) ^ k0, x1 = (uint32_t)c;
+    x2 = __builtin_amdgcn_bitop3_b32((uint32_t)(b >> 32), x3, k1, 0x96);
+    x3 = (uint32_t)b;
+    k0 += kPhiloxW0;
+    k1 += kPhiloxW1;
+#pragma unroll
+    for (int r = 2; r < 10; ++r) {
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * x0;
+        const uint64_t p1 = (uint64_t)kPhiloxM1 * x2;
+        const uint32_t y0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), x1, k0, 0x96);
+        const uint32_t y2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), x3, k1, 0x96);
+        x0 = y0;
+        x1 = (uint32_t)p1;
+        x2 = y2;
+        x3 = (uint32_t)p0;
+        k0 += kPhiloxW0;
+        k1 += kPhiloxW1;
+    }
+    out[0] = x0;
+    out[1] = x1;
+    out[2] = x2;
+    out[3] = x3;
+}
+
 // The 64-bit word h (0 or 1) of a block: words 2h (low half) and 2h + 1.
 __device__ __forceinline__ uint64_t block_word64(const uint32_t B[4], uint32_t h) {
     return h ? ((uint64_t)B[2] | ((uint64_t)B[3] << 32)) : ((uint64_t)B[0] | ((uint64_t)B[1] << 32));

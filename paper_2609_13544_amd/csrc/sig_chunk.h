@@ -1479,7 +1479,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
             const ChunkCtx x = ctx(pair_of(c0 + i), c0 + i);
             const InjDesc &d = inj[x.pair];
             const bool none = !d.all && d.T == 0;
-            const uint32_t f = none ? 0u : dpp_sum_u32(inject_span<true>(d, (uint64_t)x.off, x.len, queue));
+            const uint32_t f = none ? 0u : dpp_sum_u32(inject_span<true>(d, (uint64_t)x.off, x.len, queue, InjList{}));
             __builtin_amdgcn_s_waitcnt(0);
             if (lane == 0) sh.rcnt[wave][0] = f;
             __syncthreads();

@@ -1,0 +1,66 @@
+"""GPU parity of the injector at the edges of its segments, groups and queues
+and of the listed random values: every flip, value and count against the
+oracle, bit for bit."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_13544_amd as P
+from tests.parity import special_pair, to_device, to_host_bits
+
+pytestmark = pytest.mark.gpu
+
+MASKS = {0: 0x7F800000, 1: 0x7FFF, 2: 0x00FF}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    assert torch.cuda.is_available(), "GPU tests need the MI355X"
+    P.lib()
+    assert oracle.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+def _same(x, gb, code, seed, rate, model, cnt, ctx):
+    ref = gb.copy()
+    assert cnt == oracle.inject_model(ref, dtype=code, seed=seed, rate=rate, model=model, mask=MASKS[code]), ctx
+    assert np.array_equal(to_host_bits(x), ref), ctx
+
+
+@pytest.mark.parametrize("code", [0, 1, 2])
+@pytest.mark.parametrize("n", [1, 31, 33, 8191, 8192, 8193, 65537, (1 << 20) - 1, (1 << 21) + 17])
+def test_segments(n, code):
+    """Rates with lists, with copies, at the candidate path's limit (2^-8) and beyond."""
+    gb, _ = special_pair(n, code, seed=n % 1000 + code)
+    for rate in (1e-5, 3e-3, 0.0039, 0.0040, 0.3, 1.0):
+        for model in (P.MODEL_BITFLIP, P.MODEL_VALUE):
+            x = to_device(gb, code)
+            cnt = P.inject_model(x, 99 + n, rate, model, MASKS[code])
+            _same(x, gb, code, 99 + n, rate, model, cnt, f"n={n} rate={rate} model={model}")
+
+
+def test_many_segments_and_overlapping_items():
+    """A batch of large items (full segments) with listed values, and two
+    random-value items on disjoint halves of one allocation beside one on a
+    tensor that another item rewrites with its own bits (rate 0)."""
+    n = 1 << 22
+    items, hosts = [], []
+    for k, model in enumerate((P.MODEL_VALUE, P.MODEL_NAN, P.MODEL_VALUE, P.MODEL_BITFLIP) * 2):
+        gb, _ = special_pair(n, 0, seed=k, special_frac=0.0)
+        hosts.append((gb, model))
+        items.append((to_device(gb, 0), 1000 + k, 1e-4, MASKS[0], model))
+    counts = P.inject_batched(items)
+    for k, ((gb, model), it) in enumerate(zip(hosts, items)):
+        _same(it[0], gb, 0, 1000 + k, 1e-4, model, counts[k], f"item {k}")
+    gb, _ = special_pair(200000, 0, seed=5, special_frac=0.0)
+    x = to_device(gb, 0)
+    a, b = x[:100000], x[100000:]
+    counts = P.inject_batched([(a, 7, 1e-3, MASKS[0], P.MODEL_VALUE), (b, 8, 1e-3, MASKS[0], P.MODEL_VALUE),
+                               (x, 9, 0.0, MASKS[0], P.MODEL_BITFLIP)])
+    _same(a, gb[:100000], 0, 7, 1e-3, P.MODEL_VALUE, counts[0], "first half")
+    _same(b, gb[100000:], 0, 8, 1e-3, P.MODEL_VALUE, counts[1], "second half")
+    assert counts[2] == 0
