@@ -33,7 +33,8 @@ __device__ __forceinline__ void store_bits(void *x, int dtype, int64_t i, uint32
 
 __global__ void __launch_bounds__(kBlock) corrupt_positions_kernel(void *x, int64_t n, int dtype, uint64_t seed,
                                                                    int model, int64_t num_pos, uint64_t mask,
-                                                                   int popc, int64_t *out_pos) {
+                                                                   int popc, int64_t *out_pos,
+                                                                   uint32_t *done) {
     __shared__ int64_t pos[PEAT_MAX_POSITIONS], src[PEAT_MAX_POSITIONS];
     __shared__ uint64_t set[kSet];
     __shared__ int64_t cp[kBlock], cs[kBlock];
@@ -82,6 +83,7 @@ __global__ void __launch_bounds__(kBlock) corrupt_positions_kernel(void *x, int6
     }
     if (!complete) {                       // unreachable in practice; reported by the host
         for (int64_t m = tid; m < num_pos; m += kBlock) out_pos[m] = -1;
+        signal_host(done);
         return;
     }
     // every source and old value is read before any position is written
@@ -106,6 +108,7 @@ __global__ void __launch_bounds__(kBlock) corrupt_positions_kernel(void *x, int6
         store_bits(x, dtype, pos[m], val[m]);
         out_pos[m] = pos[m];
     }
+    signal_host(done);
 }
 
 // Round-to-nearest-even of f32 bits to binary16 (the hardware conversion,
@@ -141,11 +144,11 @@ __global__ void __launch_bounds__(kBlock) cast_round_kernel(uint32_t *x, int64_t
 }  // namespace
 
 hipError_t launch_corrupt_positions(void *x, int64_t n, int dtype, uint64_t seed, int model, int64_t num_pos,
-                                    uint64_t mask, int64_t *d_positions, hipStream_t s) {
+                                    uint64_t mask, int64_t *positions, uint32_t *done, hipStream_t s) {
     if (num_pos <= 0) return hipSuccess;
     const uint64_t m = model == PEAT_MODEL_BITFLIP ? mask : 1;
     hipLaunchKernelGGL(corrupt_positions_kernel, dim3(1), dim3(kBlock), 0, s, x, n, dtype, seed, model, num_pos, m,
-                       __builtin_popcountll(m), d_positions);
+                       __builtin_popcountll(m), positions, done);
     return hipGetLastError();
 }
 

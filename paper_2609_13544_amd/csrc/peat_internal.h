@@ -105,6 +105,7 @@ struct SigParams {
     ChunkPartial *partials;        // one per chunk
     peat_signature_t *outs;        // one per pair (device)
     int64_t *inj_counts;           // flips per pair (device), fused injection only
+    uint32_t *done;                // host memory, one word per pair set once its record is out, or NULL
     int32_t count;                 // pairs
     int32_t lo, hi, nbins;
     int32_t nthr;                  // real thresholds
@@ -205,12 +206,24 @@ struct TopkParams {
     unsigned long long *fill;    // entries and segments handed out
     uint64_t cap[2];
     peat_topk_t *outs;           // one per pair
+    uint32_t *done;              // host memory, one word per pair set by the call's last kernel, or NULL
     int32_t count;               // pairs
     int32_t num, den;
     int32_t level;               // digit of a digit pass
     int32_t single;              // one pair, described by `one` (descs and chunk_pair unused)
     SigDesc one;
 };
+
+// Tells a host that polls `done` (pinned memory) that what this block wrote
+// there is complete, and what it wrote to device memory is visible to whatever
+// the host starts next, on any stream (the release covers the block's L2).
+// Called by every thread of the block, after its last access.
+__device__ __forceinline__ void signal_host(uint32_t *done) {
+    if (!done) return;
+    __builtin_amdgcn_s_waitcnt(0);               // each wave's own stores
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Kernel launchers (defined in the .hip translation units).
 // One launch per kind present: chunks of each kind form one contiguous range
@@ -231,7 +244,7 @@ hipError_t launch_inject(const InjParams &p, int64_t total_segs, hipStream_t s);
 hipError_t launch_inject_sum(const InjParams &p, hipStream_t s);
 hipError_t launch_inject_apply(const InjParams &p, int64_t total_segs, hipStream_t s);
 hipError_t launch_corrupt_positions(void *x, int64_t n, int dtype, uint64_t seed, int model, int64_t num_pos,
-                                    uint64_t mask, int64_t *d_positions, hipStream_t s);
+                                    uint64_t mask, int64_t *positions, uint32_t *done, hipStream_t s);
 hipError_t launch_cast_round(void *x, int64_t n, int to_dtype, hipStream_t s);
 hipError_t launch_stream_read(const void *buf, int64_t bytes, uint32_t *sink, hipStream_t s);
 // The top-k selection of a batch, stream-ordered: the small pairs' records and

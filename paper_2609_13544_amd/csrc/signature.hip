@@ -316,8 +316,7 @@ __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
     // one output word per thread, the waves in order; two stores per block.
     // Every thread forms every merged value (broadcast LDS reads) and keeps
     // its own word by selects, so the waves do not diverge here.
-    if (tid > kOutWords) return;
-    const int t = tid;
+    const int t = min(tid, kOutWords);
     const int ks = min(max(t - kW_sums, 0), 5);
     uint64_t add = 0, nanp = 0, MU = 0;
     double S = 0.0, MA = -1.0, MR = -1.0;
@@ -347,10 +346,11 @@ __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
     word = t == kW_maxrel ? (IR >= 0 ? (uint64_t)__double_as_longlong(MR) : qnan) : word;
     word = t == kW_ixrel ? (uint64_t)IR : word;
     word = ((t >= kW_sums) & (t < kW_sums + 6)) ? (uint64_t)__double_as_longlong(S) : word;
-    if (t < kOutWords)
+    if (tid < kOutWords)
         reinterpret_cast<uint64_t *>(P.outs + pair)[t] = word;
-    else if (P.inj_counts)
+    else if (tid == kOutWords && P.inj_counts)
         P.inj_counts[pair] = (int64_t)word;
+    signal_host(P.done ? P.done + pair : nullptr);
 }
 
 }  // namespace

@@ -506,6 +506,7 @@ __global__ void __launch_bounds__(kBig) topk_start(TopkParams P) {
             write_record(P.outs + pair, nv, k, need, T, t + __builtin_ldexp(xd, (b0 != 0 ? b0 : 1) - 1075));
             P.state[pair].status = kTopkDone;
         }
+        signal_host(P.done ? P.done + pair : nullptr);
         return;
     }
 
@@ -929,7 +930,10 @@ __global__ void __launch_bounds__(kBig) topk_resolve(TopkParams P) {
     __shared__ ResolveShared sh;
     const int pair = blockIdx.x, tid = threadIdx.x;
     const TopkState st = P.state[pair];
-    if (st.status == kTopkDone) return;
+    if (st.status == kTopkDone) {                             // a small pair
+        signal_host(P.done ? P.done + pair : nullptr);
+        return;
+    }
     const SigDesc d = desc_of(P, pair);
     uint64_t *xs = P.xsum + (size_t)pair * 2 * kBins0;
     // leaves the pair to the digit passes
@@ -942,6 +946,7 @@ __global__ void __launch_bounds__(kBig) topk_resolve(TopkParams P) {
             P.state[pair].status = kTopkOpen;
             atomicAdd(P.open, 1u);
         }
+        signal_host(P.done ? P.done + pair : nullptr);
     };
     const uint64_t nv = (uint64_t)d.n - P.counts[2 * pair], na = P.counts[2 * pair + 1];
     const uint64_t k = top_count(nv, P);
@@ -1063,6 +1068,7 @@ __global__ void __launch_bounds__(kBig) topk_resolve(TopkParams P) {
         write_record(P.outs + pair, nv, k, need, T, sum);
         P.state[pair].status = kTopkDone;
     }
+    signal_host(P.done ? P.done + pair : nullptr);
 }
 
 // ---- digit passes ------------------------------------------------------------------

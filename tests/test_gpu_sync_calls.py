@@ -1,0 +1,56 @@
+"""Synchronous calls on alternating streams: their results are complete, and
+what they wrote to device memory is there for other streams, when they return;
+pair counts at and beside the number up to which the host polls for the end."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_13544_amd as P
+from tests.parity import float_to_bits, to_device
+from tests.test_gpu_topk import assert_topk
+
+pytestmark = pytest.mark.gpu
+
+POLLED = 64                           # pairs of a call whose end the host polls for
+SIZES = [100, (1 << 14) + 1, 0, 70001]
+
+
+@pytest.mark.parametrize("count", [1, 2, POLLED, POLLED + 1])
+def test_alternating_streams(count):
+    rng = np.random.default_rng(count)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    pairs, bits = [], []
+    for k in range(count):
+        n = SIZES[(k + 1) % len(SIZES)]
+        g = rng.standard_normal(n)
+        gb, tb = float_to_bits(g, 0).copy(), float_to_bits(g * (1 + 1e-3 * rng.standard_normal(n)), 0).copy()
+        bits.append((gb, tb))
+        pairs.append((to_device(gb, 0), to_device(tb, 0)))
+    ref = P.signature_batched(pairs, (-40, 24, 64))
+    want = [oracle.topk(gb, tb, dtype=0, num=1, den=10) for gb, tb in bits]
+    torch.cuda.synchronize()
+    for rep in range(6):
+        with torch.cuda.stream(streams[rep & 1]):
+            assert repr(P.signature_batched(pairs, (-40, 24, 64))) == repr(ref)
+        with torch.cuda.stream(streams[1 - (rep & 1)]):
+            for got, w in zip(P.topk_mean_batched(pairs, 1, 10), want):
+                assert_topk(got, w)
+
+
+@pytest.mark.parametrize("n", [64, 10007, 1 << 20])
+def test_writes_seen_by_another_stream(n):
+    x = torch.randn(n, device="cuda")
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for seed in range(8):
+        y = x.clone()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(a):
+            pos = P.corrupt_positions(y, seed, P.MODEL_BITFLIP, 32, 1 << 30)
+        with torch.cuda.stream(b):
+            diff = torch.nonzero(y.view(torch.int32) != x.view(torch.int32)).flatten()
+        b.synchronize()
+        assert sorted(pos) == diff.tolist()
