@@ -222,7 +222,14 @@ __device__ __forceinline__ void signal_host(uint32_t *done) {
     if (!done) return;
     __builtin_amdgcn_s_waitcnt(0);               // each wave's own stores
     __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0) {
+        // The L2's dirty lines go out, and are out before the word is: the
+        // wait is explicit, because the compiler drops the fence's own when it
+        // knows of no access in flight, and does not count the write-back.
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+        __builtin_amdgcn_s_waitcnt(0);
+        __hip_atomic_store(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // Kernel launchers (defined in the .hip translation units).

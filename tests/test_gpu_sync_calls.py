@@ -54,3 +54,18 @@ def test_writes_seen_by_another_stream(n):
             diff = torch.nonzero(y.view(torch.int32) != x.view(torch.int32)).flatten()
         b.synchronize()
         assert sorted(pos) == diff.tolist()
+
+
+def test_many_calls():
+    """Many short calls in a row: every record is whole when its call returns
+    (the end of a call was once told before the last of its record was out)."""
+    rng = np.random.default_rng(7)
+    pairs = []
+    for k in range(64):
+        g = rng.standard_normal(5000 + k)
+        t = g * (1 + 1e-3 * rng.standard_normal(5000 + k))
+        pairs.append((torch.from_numpy(g).float().cuda(), torch.from_numpy(t).float().cuda()))
+    want = P.signature_batched(pairs, (-40, 24, 64))
+    for rep in range(400):
+        for (g, t), w in zip(pairs, want):
+            assert P.signature(g, t, (-40, 24, 64)) == w, rep
