@@ -275,10 +275,21 @@ int same_type_pairs(const peat_pair_t *pairs, int32_t count, std::vector<peat_mi
     return PEAT_OK;
 }
 
+// Whether a call of `chunks` chunks gives the pieces of a pair's chunks blocks
+// of their own, and the pair's descriptor then.
+inline void set_pieces(SigDesc &sd, int64_t chunks) {
+    sd.pieces = pieces_log2_for(sd.chunk_log2);
+    if (sd.pieces == 0 || chunks > kSplitChunks || sd.nchunks > kSplitPairChunks) return;
+    sd.chunk_log2 -= kPieceLog2;
+    sd.nchunks = (int32_t)((sd.n + (int64_t(1) << sd.chunk_log2) - 1) >> sd.chunk_log2);
+    sd.pieces = -kPieceLog2;
+}
+
 // Partition every pair into chunks; the chunks of each kind (golden/test
 // type combination) get one contiguous range [range[kind], range[kind + 1])
 // of the global numbering (one launch per kind).
-int build_descs(const peat_mixed_pair_t *pairs, int32_t count, std::vector<SigDesc> &descs,
+// split: the pieces of the chunks of a small batch count as chunks.
+int build_descs(const peat_mixed_pair_t *pairs, int32_t count, bool split, std::vector<SigDesc> &descs,
                 int64_t range[kKinds + 1], int64_t *total_out) {
     descs.assign((size_t)count, SigDesc{});
     // Within a kind the pairs with the largest chunks come first, so that a
@@ -296,7 +307,11 @@ int build_descs(const peat_mixed_pair_t *pairs, int32_t count, std::vector<SigDe
     }
     for (int i = 0; i < kKinds * kClasses; ++i) start[i + 1] += start[i];
     for (int k = 0; k < count; ++k) order[start[key[k]]++] = k;
-    int64_t total = 0;
+    int64_t total = 0, chunks = 0;
+    for (int k = 0; split && k < count; ++k) {
+        const int lg = chunk_log2_for(pairs[k].n);
+        chunks += (pairs[k].n + (int64_t(1) << lg) - 1) >> lg;
+    }
     int pos = 0;
     for (int kind = 0; kind < kKinds; ++kind) {
         range[kind] = total;
@@ -312,7 +327,8 @@ int build_descs(const peat_mixed_pair_t *pairs, int32_t count, std::vector<SigDe
             const int64_t nch = (sd.n + (int64_t(1) << sd.chunk_log2) - 1) >> sd.chunk_log2;
             sd.first_chunk = total;
             sd.nchunks = (int32_t)nch;
-            total += nch;
+            if (split) set_pieces(sd, chunks);
+            total += split ? (int64_t)sd.nchunks : nch;
         }
     }
     range[kKinds] = total;
@@ -394,7 +410,7 @@ int signature_core(const peat_mixed_pair_t *pairs, int32_t count, const peat_bin
     std::vector<SigDesc> descs;
     int64_t total = 0;
     int64_t range[kKinds + 1];
-    if ((rc = build_descs(pairs, count, descs, range, &total))) return rc;
+    if ((rc = build_descs(pairs, count, true, descs, range, &total))) return rc;
 
     // A lone pair without injection travels in the kernel arguments: nothing
     // to stage, and no copy ahead of the chunk pass.
@@ -789,7 +805,7 @@ int topk_core(const peat_mixed_pair_t *pairs, int32_t count, int32_t num, int32_
     std::vector<SigDesc> descs;
     int64_t total = 0;
     int64_t range[kKinds + 1];
-    if ((rc = build_descs(pairs, count, descs, range, &total))) return rc;
+    if ((rc = build_descs(pairs, count, false, descs, range, &total))) return rc;
 
     bool large = false;                      // some pair needs more than the start kernel
     for (int k = 0; k < count; ++k) large = large || pairs[k].n > kTopkSmall;
@@ -949,7 +965,25 @@ int signature_noalloc_core(const peat_pair_t *pairs, int32_t count, const peat_b
     if (!d_outs) return fail(PEAT_EINVAL, "d_outs is NULL");
     int64_t range[kKinds + 1];
     int64_t cursor[kKinds * kClasses];
-    int64_t total = 0;
+    int64_t total = 0, chunks = 0;
+    for (const int64_t c : per_class) chunks += c;
+    if (count > kSplitChunks) chunks = INT64_MAX;         // (empty pairs: descriptors only)
+    // (a batch this small fits the scratch array also with its pieces apart:
+    // split chunks are few, and smaller ones are not split)
+    static_assert((kSplitChunks << kPieceLog2) * (sizeof(ChunkPartial) + sizeof(int32_t)) <
+                      (size_t)PEAT_NOALLOC_SCRATCH_BYTES / 8,
+                  "pieces of a small batch");
+    if (chunks <= kSplitChunks)
+        for (int k = 0; k < count; ++k) {
+            SigDesc sd{};
+            sd.n = pairs[k].n;
+            sd.chunk_log2 = chunk_log2_for(sd.n);
+            const int cl = kMaxChunkLog2 - sd.chunk_log2;
+            const int64_t nch = (sd.n + (int64_t(1) << sd.chunk_log2) - 1) >> sd.chunk_log2;
+            sd.nchunks = (int32_t)nch;
+            set_pieces(sd, chunks);
+            per_class[pair_kind(pairs[k].dtype, pairs[k].dtype) * kClasses + cl] += sd.nchunks - nch;
+        }
     for (int kind = 0; kind < kKinds; ++kind) {
         range[kind] = total;
         for (int c = 0; c < kClasses; ++c) {
@@ -988,6 +1022,7 @@ int signature_noalloc_core(const peat_pair_t *pairs, int32_t count, const peat_b
         sd.chunk_log2 = chunk_log2_for(sd.n);
         sd.nchunks = (int32_t)((sd.n + (int64_t(1) << sd.chunk_log2) - 1) >> sd.chunk_log2);
         int64_t &cur = cursor[kind * kClasses + (kMaxChunkLog2 - sd.chunk_log2)];
+        set_pieces(sd, chunks);
         sd.first_chunk = cur;
         cur += sd.nchunks;
         if (b.count == kFillDescs || k + 1 == count) {

@@ -259,7 +259,7 @@ struct alignas(16) Shared {
     uint32_t elems[kWaves][kElemCap];      // element indices (within the chunk) for the generic path
     // generic-path sums of a^2, g^2, t^2 and g*t, one column per lane
     double gsum[4][kBlock];
-    double rd[kWaves][6];
+    double racc[kWaves][8];                  // sums of the chunk's earlier pieces (wave, total)
     double rmax[kWaves][2];
     uint32_t rix[kWaves][5];               // abs, rel, ulp, first_nan, first_valid
     uint32_t rmu[kWaves];
@@ -1024,6 +1024,41 @@ __device__ __forceinline__ double dpp_sum(double v) {
     dsum_step<kDppBcast31, 0xC>(v);
     return lane63_f64(v);
 }
+// The wave's sums of six binary64 values, total k in lane k (lanes 6 and 7 hold
+// totals 4 and 5 again, and the other lanes repeat the first eight); a fixed
+// order.  In the first three steps a lane keeps one of two values and hands
+// the other to its partner, so the steps halve the values as they halve the
+// lanes: 12 additions in place of the 36 of six separate reductions, and half
+// the code (the end of a piece runs seldom: what it costs is mostly the fetch
+// of its instructions).
+constexpr int kDppXor3 = 0x1B;           // quad_perm [3, 2, 1, 0]
+constexpr int kDppRor8 = 0x128;          // row_ror:8, the lane 8 away in its row
+__device__ __forceinline__ double half_sum(double v, bool wide) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    // both halves of the wave (of each pair of rows), in every lane
+    const auto l = wide ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                        : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = wide ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                        : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0])) +
+           __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+}
+__device__ __forceinline__ double dpp_sum6(const double (&v)[6], int lane) {
+    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0, b2 = (lane & 4) != 0;
+    double w[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double mine = b0 ? v[2 * k + 1] : v[2 * k], other = b0 ? v[2 * k] : v[2 * k + 1];
+        w[k] = mine + dpp_f64<kDppXor1, 0xF>(0.0, other);
+    }
+    const double z0 = (b1 ? w[1] : w[0]) + dpp_f64<kDppXor2, 0xF>(0.0, b1 ? w[0] : w[1]);
+    const double z1 = w[2] + dpp_f64<kDppXor2, 0xF>(0.0, w[2]);
+    const double other = b2 ? z0 : z1;
+    double r = (b2 ? z1 : z0) + dpp_f64<kDppXor3, 0xF>(0.0, dpp_f64<kDppHalfMirror, 0xF>(0.0, other));
+    r += dpp_f64<kDppRor8, 0xF>(0.0, r);
+    return half_sum(half_sum(r, false), true);
+}
 // Wave sum of a 32-bit count (at most 2^31 in total), as a scalar; zero
 // without any data movement when every lane holds zero.
 __device__ __forceinline__ uint32_t dpp_sum_u32(uint32_t v) {
@@ -1087,6 +1122,7 @@ struct ChunkCtx {
     const char *gbase, *tbase;               // first element of golden and test
     int32_t pair;
     int32_t log2;                            // chunk size of the pair
+    int32_t plog2;                           // size of a piece (log2; the chunk's when it is in one piece)
     uint32_t len;                            // elements
     uint32_t nsuper;                         // full super-steps
 };
@@ -1099,8 +1135,9 @@ struct ChunkCtx {
 // per block.
 //
 // Only the binary64 sums depend on how elements are grouped, so only they
-// are reduced per chunk, per wave, with no block barrier: each wave writes its
-// six totals into the chunk record (one store).  Everything else (counts,
+// are reduced per piece, per wave, with no block barrier: each wave adds its
+// six totals to those of the chunk's earlier pieces and writes them into the
+// chunk record (one store) when the chunk ends.  Everything else (counts,
 // maxima with their lowest index, first indices, the ULP sum, the histogram)
 // is exact and independent of grouping, so it is carried over the block's run
 // of consecutive chunks of one pair (indices relative to the run) and reduced
@@ -1130,7 +1167,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
     struct PairS {
         const char *g, *t;
         int64_t n, first;
-        int32_t pair, log2, nchunks;
+        int32_t pair, log2, plog2, nchunks;
     };
     auto pair_of = [&](int64_t c) {
         PairS d;
@@ -1149,6 +1186,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         d.n = (int64_t)uniform_u64((uint64_t)dm.n);
         d.first = (int64_t)uniform_u64((uint64_t)dm.first_chunk);
         d.log2 = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)dm.chunk_log2);
+        d.plog2 = d.log2 - max((int32_t)__builtin_amdgcn_readfirstlane((uint32_t)dm.pieces), 0);
         d.nchunks = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)dm.nchunks);
         return d;
     };
@@ -1157,6 +1195,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         x.gchunk = P.chunk_base + c;
         x.pair = d.pair;
         x.log2 = d.log2;
+        x.plog2 = d.plog2;
         x.off = (x.gchunk - d.first) << d.log2;
         const int64_t rest = d.n - x.off;
         x.len = (uint32_t)(rest < (int64_t(1) << d.log2) ? rest : (int64_t(1) << d.log2));
@@ -1288,37 +1327,40 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         __builtin_amdgcn_s_waitcnt(0);
     };
 
-    // End of a chunk: the wave's binary64 sums.  Fast-path t^2 and
+    // The wave's six binary64 totals, total k in lane k.  Fast-path t^2 and
     // g*t come from their exact per-element identities, then the generic
-    // path's direct sums are added; a fixed order per lane.
-    auto chunk_end = [&](const ChunkCtx &c, uint32_t ib, bool run_end) {
+    // path's direct sums are added; a fixed order per lane.  The totals of a
+    // chunk's pieces are added in order.
+    auto wave_sums = [&](bool folded) {
         GenAcc ga;
         ga.load(sh, tid);
+        const double f_t2 = (L.s_g2 + 2.0 * L.s_ge) + L.s_sq;
+        const double f_gt = L.s_g2 + L.s_ge;
+        const double lane_sums[6] = {L.s_abs, L.s_sq + ga.sq, L.s_rel, L.s_g2 + ga.g2, f_t2 + ga.t2, f_gt + ga.gt};
+        const double sum = dpp_sum6(lane_sums, lane);
+        reset_sums();
+        return folded ? sh.racc[wave][lane & 7] + sum : sum;
+    };
+    // The end of a piece within a chunk.
+    auto fold_sums = [&](bool folded) {
+        const double sum = wave_sums(folded);
+        if (lane < 8) sh.racc[wave][lane] = sum;
+    };
+    // End of a chunk.
+    auto chunk_end = [&](const ChunkCtx &c, uint32_t ib, bool run_end, bool folded) {
         // the first ordinary element of this lane in the chunk
         if (Un.first != kNone) {
             L.first_valid = min(L.first_valid, ib + (Un.first * kBlock + tid) * VEC);
             Un.first = kNone;
         }
-        ChunkPartial *out = partials + c.gchunk;
-        {
-            const double f_t2 = (L.s_g2 + 2.0 * L.s_ge) + L.s_sq;
-            const double f_gt = L.s_g2 + L.s_ge;
-            const double lane_sums[6] = {L.s_abs, L.s_sq + ga.sq, L.s_rel, L.s_g2 + ga.g2, f_t2 + ga.t2, f_gt + ga.gt};
-            // One store per wave: lanes 0-5 write its six totals (wave 0: lane 0
-            // the run-end flag, lanes 1-6 the totals).  A chunk that does not
-            // end the run writes nothing else: its record's exact fields are
-            // left as they are and the finalize skips them.
-            const int w0 = wave == 0 ? 1 : 0;
-            uint64_t word = run_end ? 1u : 0u;
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                const double v = dpp_sum(lane_sums[k]);
-                if (lane == k + w0) word = (uint64_t)__double_as_longlong(v);
-            }
-            uint64_t *row = reinterpret_cast<uint64_t *>(out) + (w0 ? 0 : 1 + 6 * wave);
-            if (lane < 6 + w0) row[lane] = word;
-        }
-        reset_sums();
+        // One store per wave: lanes 0-5 write its six totals and lane 6 of
+        // wave 0 the run-end flag.  A chunk that does not end the run writes
+        // nothing else: its record's exact fields are left as they are and
+        // the finalize skips them.
+        uint64_t word = (uint64_t)__double_as_longlong(wave_sums(folded));
+        word = lane == 6 ? (run_end ? 1u : 0u) : word;
+        uint64_t *row = reinterpret_cast<uint64_t *>(partials + c.gchunk);
+        if (lane < (wave == 0 ? 7 : 6)) row[lane == 6 ? 0 : 1 + 6 * wave + lane] = word;
     };
 
     // End of a run: counts, maxima, first indices, ULP sum and histogram of
@@ -1511,6 +1553,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
         const bool run_end = !more || nxt.pair != cur.pair;
         if (i == run_first) run_off = cur.off;
         const uint32_t ib = (uint32_t)(i - run_first) << cur.log2;
+        bool folded = false;                     // racc holds the sums of the chunk's earlier pieces
         if (cur.nsuper > 0) {
             if (!pre) load(ga, ta, cur, 0);
             // Pairs of super-steps are pipelined: each half step issues one
@@ -1534,9 +1577,19 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
                 load_at(ga, ta, hop ? nxt.gbase : cur.gbase, hop ? nxt.tbase : cur.tbase, hop ? nxt.len : cur.len,
                         hop ? 0u : (last && !odd ? s + 1 : s + 2));
                 step(gb, tb, s + 1, ib);
+                // the end of a piece that is not the chunk's: a multiple of
+                // 2^kSplitMinLog2 / 4 elements, and so of two super-steps
+                static_assert((1 << (kSplitMinLog2 - kPieceLog2)) % (2 * SUPER) == 0, "pieces are whole pairs of super-steps");
+                const uint32_t at = (s + 2) * SUPER;
+                const bool piece_end = (at & ((1u << cur.plog2) - 1u)) == 0 && at < cur.len;
                 // the deferred list must hold the next two super-steps (or the
-                // odd last one and the ragged rest's vectors)
-                if (ndef > kDeferCap - 2 * U) rest(cur, ib, 0, false);
+                // odd last one and the ragged rest's vectors), and its
+                // elements are part of their piece's sums
+                if (__builtin_expect(ndef > (piece_end ? 0u : (uint32_t)(kDeferCap - 2 * U)), 0)) rest(cur, ib, 0, false);
+                if (__builtin_expect(piece_end, 0)) {
+                    fold_sums(folded);
+                    folded = true;
+                }
             }
             if (odd) {
                 step(ga, ta, npair, ib);
@@ -1560,7 +1613,7 @@ __device__ __forceinline__ void chunk_loop(const SigParams &P, Shared &sh, const
             L.s_ulp32 = 0;
         }
         rest(cur, ib, (v0 + nv) * (kBlock * VEC), true);
-        chunk_end(cur, ib, run_end);
+        chunk_end(cur, ib, run_end, folded);
         if (run_end) {
             run_end_reduce(cur, run_off);
             run_first = i + 1;

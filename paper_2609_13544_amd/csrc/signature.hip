@@ -104,15 +104,17 @@ struct FinAcc {
     uint64_t mu, sulp, flips;
     uint64_t cn[kCnt + PEAT_MAX_THRESHOLDS];
 };
-__device__ __forceinline__ void fin_merge(FinAcc &A, const RecF &r, bool have) {
+__device__ __forceinline__ void fin_sums(FinAcc &A, const double (&s)[kWaves][6], bool have) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-        double t = r.s[0][k];
+        double t = s[0][k];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) t += r.s[w][k];
+        for (int w = 1; w < kWaves; ++w) t += s[w][k];
         // the sum starts at +0 and never becomes -0, so adding +0 is exact
         A.s[k] += have ? t : 0.0;
     }
+}
+__device__ __forceinline__ void fin_merge(FinAcc &A, const RecF &r, bool have) {
     const bool e = have && r.end != 0;
     lex_take(A.ma, A.ia, r.ma, e ? r.ia : int64_t(-1));
     lex_take(A.mr, A.ir, r.mr, e ? r.ir : int64_t(-1));
@@ -179,18 +181,22 @@ __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
     const int pair = blockIdx.x;
     // the pair's fields (uniform: scalar loads from the arguments or the table)
     int64_t n, first;
-    int m;
+    int m, pieces;
     if (P.single) {
         n = P.one.n;
         first = P.one.first_chunk;
         m = P.one.nchunks;
+        pieces = P.one.pieces;
     } else {
         n = P.descs[pair].n;
         first = P.descs[pair].first_chunk;
         m = P.descs[pair].nchunks;
+        pieces = P.descs[pair].pieces;
     }
     n = (int64_t)uniform_u64((uint64_t)n);
     m = (int)__builtin_amdgcn_readfirstlane((uint32_t)m);
+    // the records are those of chunks' pieces: added up to the chunks' first
+    const bool split = (int)__builtin_amdgcn_readfirstlane((uint32_t)pieces) < 0;
     const ChunkPartial *parts = P.partials + (int64_t)uniform_u64((uint64_t)first);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nb = P.nbins;
@@ -240,7 +246,29 @@ __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
 #pragma unroll
         for (int k = 0; k < kRecParts; ++k) stage[tid + k * kBlock] = v[k];
         __syncthreads();
-        fin_merge(A, load_rec(srec[min(tid, cnt - 1)]), tid < cnt);
+        if (!split) {
+            const RecF r = load_rec(srec[min(tid, cnt - 1)]);
+            fin_sums(A, r.s, tid < cnt);
+            fin_merge(A, r, tid < cnt);
+        } else {
+            // chunk c of the pair belongs to thread c % kBlock, as above: the
+            // batch's chunks to one wave
+            static_assert(kBlock >> kPieceLog2 == 64, "a batch of records is one wave of chunks");
+            const int r0 = lane << kPieceLog2;
+            if (wave == ((base / kBlock) & (kWaves - 1)) && r0 < cnt) {
+                double s[kWaves][6];
+#pragma unroll 1
+                for (int j = 0; j < 1 << kPieceLog2 && r0 + j < cnt; ++j) {
+                    const RecF r = load_rec(srec[r0 + j]);
+#pragma unroll
+                    for (int w = 0; w < kWaves; ++w)
+#pragma unroll
+                        for (int k = 0; k < 6; ++k) s[w][k] = j == 0 ? r.s[w][k] : s[w][k] + r.s[w][k];
+                    fin_merge(A, r, true);
+                }
+                fin_sums(A, s, true);
+            }
+        }
         // bit u: record wave + 4u exists and ends a run (only those rows were written)
         const uint64_t em = __ballot(wave + lane * kWaves < cnt && srec[min(wave + lane * kWaves, cnt - 1)].run_end != 0);
 #pragma unroll
