@@ -50,39 +50,13 @@ __device__ __forceinline__ int slot_word(int s, int nb) {
                   : (s == 1 ? kW_hunder : (s == nb + 2 ? kW_hover : (s <= nb + 1 ? kW_hist + s - 2 : kW_hist + s - 3)));
 }
 
-// The fields of a chunk record that the finalize reads.
 constexpr int kRecParts = (int)(sizeof(ChunkPartial) / 16);    // 16-byte parts of a record
 static_assert(sizeof(ChunkPartial) % 16 == 0, "records are copied in 16-byte parts");
-struct RecF {
-    double s[kWaves][6];
-    int64_t end, ia, ir, iu, fn;
-    double ma, mr;
-    uint64_t su;
-    uint32_t mu, fl;
-    uint32_t cn[kCnt + PEAT_MAX_THRESHOLDS];
-};
-__device__ __forceinline__ RecF load_rec(const ChunkPartial &p) {
-    RecF r;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w)
-#pragma unroll
-        for (int k = 0; k < 6; ++k) r.s[w][k] = p.s[w][k];
-    r.end = p.run_end;
-    r.ma = p.max_abs;
-    r.mr = p.max_rel;
-    r.ia = p.ix_abs;
-    r.ir = p.ix_rel;
-    r.iu = p.ix_ulp;
-    r.fn = p.first_nan;
-    r.su = p.sum_ulp;
-    r.mu = p.max_ulp;
-    r.fl = p.flips;
-#pragma unroll
-    for (int k = 0; k < kCnt; ++k) r.cn[k] = p.cnt[k];
-#pragma unroll
-    for (int j = 0; j < PEAT_MAX_THRESHOLDS; ++j) r.cn[kCnt + j] = p.mism[j];
-    return r;
-}
+// A record's additive words, one array: counts, mismatches, histogram.
+constexpr int kAdd = kCnt + PEAT_MAX_THRESHOLDS + kHistSlots;
+static_assert(offsetof(ChunkPartial, hist) == offsetof(ChunkPartial, cnt) + (kCnt + PEAT_MAX_THRESHOLDS) * 4 &&
+                  kAdd > 64 && kAdd <= 128,
+              "additive words: two per lane");
 
 // (value desc, index asc) maximum over entries with index >= 0.
 template <typename V>
@@ -93,90 +67,24 @@ __device__ __forceinline__ void lex_take(V &v, int64_t &ix, V ov, int64_t oi) {
     ix = take ? oi : ix;
 }
 
-// A thread's share of a pair: binary64 sums over its records in order (each
-// record's waves in order), the maxima, first NaN and counts of the records
-// that end a run (the others carry no exact fields).
-struct FinAcc {
-    double s[6];
-    double ma, mr;
-    int64_t ia, ir, iu;
-    uint64_t fn;                             // first NaN index, ~0 = none
-    uint64_t mu, sulp, flips;
-    uint64_t cn[kCnt + PEAT_MAX_THRESHOLDS];
-};
-__device__ __forceinline__ void fin_sums(FinAcc &A, const double (&s)[kWaves][6], bool have) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        double t = s[0][k];
-#pragma unroll
-        for (int w = 1; w < kWaves; ++w) t += s[w][k];
-        // the sum starts at +0 and never becomes -0, so adding +0 is exact
-        A.s[k] += have ? t : 0.0;
-    }
+// Output word of additive word i of a record.
+__device__ __forceinline__ int add_word(int i, int nb) {
+    return i < kCnt ? kW_cnt + i
+                    : (i < kCnt + PEAT_MAX_THRESHOLDS ? kW_mism + i - kCnt
+                                                      : slot_word(i - kCnt - PEAT_MAX_THRESHOLDS, nb));
 }
-__device__ __forceinline__ void fin_merge(FinAcc &A, const RecF &r, bool have) {
-    const bool e = have && r.end != 0;
-    lex_take(A.ma, A.ia, r.ma, e ? r.ia : int64_t(-1));
-    lex_take(A.mr, A.ir, r.mr, e ? r.ir : int64_t(-1));
-    lex_take(A.mu, A.iu, (uint64_t)r.mu, e ? r.iu : int64_t(-1));
-    A.fn = (e && r.fn >= 0 && (uint64_t)r.fn < A.fn) ? (uint64_t)r.fn : A.fn;
-    A.sulp += e ? r.su : 0u;
-    A.flips += have ? r.fl : 0u;
-#pragma unroll
-    for (int k = 0; k < kCnt + PEAT_MAX_THRESHOLDS; ++k) A.cn[k] += e ? r.cn[k] : 0u;
-}
-
-template <int C, int RM>
-__device__ __forceinline__ uint64_t dpp_u64(uint64_t old, uint64_t x) {
-    const uint32_t lo = dpp_u32<C, RM>((uint32_t)old, (uint32_t)x);
-    const uint32_t hi = dpp_u32<C, RM>((uint32_t)(old >> 32), (uint32_t)(x >> 32));
+__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int o) {
+    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, o), hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), o);
     return ((uint64_t)hi << 32) | lo;
 }
-// One step of the wave reductions of the three maxima and the first NaN,
-// interleaved so that their data moves overlap.  A lane that DPP does not
-// write keeps its own entry, which merges with itself unchanged.
-template <int C, int RM>
-__device__ __forceinline__ void fin_step(FinAcc &A) {
-    const double oma = dpp_f64<C, RM>(A.ma, A.ma), omr = dpp_f64<C, RM>(A.mr, A.mr);
-    const uint64_t omu = dpp_u64<C, RM>(A.mu, A.mu), ofn = dpp_u64<C, RM>(A.fn, A.fn);
-    const int64_t oia = (int64_t)dpp_u64<C, RM>((uint64_t)A.ia, (uint64_t)A.ia);
-    const int64_t oir = (int64_t)dpp_u64<C, RM>((uint64_t)A.ir, (uint64_t)A.ir);
-    const int64_t oiu = (int64_t)dpp_u64<C, RM>((uint64_t)A.iu, (uint64_t)A.iu);
-    lex_take(A.ma, A.ia, oma, oia);
-    lex_take(A.mr, A.ir, omr, oir);
-    lex_take(A.mu, A.iu, omu, oiu);
-    A.fn = ofn < A.fn ? ofn : A.fn;
-}
-__device__ __forceinline__ uint64_t lane63_u64(uint64_t v) {
-    return ((uint64_t)lane63_u32((uint32_t)(v >> 32)) << 32) | lane63_u32((uint32_t)v);
-}
-// Wave total of nonnegative integers: in 32 bits when the total is known to
-// stay below 2^31 (small, uniform), else exactly in binary64 (below 2^53).
-// No test for an all-zero wave: without that branch the compiler interleaves
-// the finalize's many totals, whose DPP steps would otherwise wait on one
-// another.
-__device__ __forceinline__ uint32_t dpp_sum_u32_all(uint32_t v) {
-    dsum_step<kDppXor1, 0xF>(v);
-    dsum_step<kDppXor2, 0xF>(v);
-    dsum_step<kDppHalfMirror, 0xF>(v);
-    dsum_step<kDppMirror, 0xF>(v);
-    dsum_step<kDppBcast15, 0xA>(v);
-    dsum_step<kDppBcast31, 0xC>(v);
-    return lane63_u32(v);
-}
-// The wave totals of a finalize's counts (kCnt + PEAT_MAX_THRESHOLDS) and
-// three tail histogram slots, all under one uniform branch.
-constexpr int kTot = kCnt + PEAT_MAX_THRESHOLDS + 3;
-__device__ __forceinline__ void wave_totals(const uint64_t (&v)[kTot], uint64_t (&t)[kTot], bool small) {
-    if (small) {
-#pragma unroll
-        for (int k = 0; k < kTot; ++k) t[k] = dpp_sum_u32_all((uint32_t)v[k]);
-    } else {
-#pragma unroll
-        for (int k = 0; k < kTot; ++k) t[k] = (uint64_t)dpp_sum((double)v[k]);
-    }
-}
 
+// One block per pair.  What bounds it is latency: one round trip for the
+// records, and the fetch of its own instructions, which every call executes
+// once; so its loops stay rolled: 8 KB of code for the 26 KB of
+// unrolled ones, and one thread per field, not per record, for what adds up.
+// 3 records 9.1 -> 7.7 us, 256 records of pieces 12.5 -> 10.5, a checkpoint's
+// 292 pairs 25 -> 20; 256 chunk records as before (10.3: their 152 KB come
+// through one compute unit).
 __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
     const int pair = blockIdx.x;
     // the pair's fields (uniform: scalar loads from the arguments or the table)
@@ -201,32 +109,27 @@ __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nb = P.nbins;
 
+    constexpr int kGroups = 2 * kWaves;               // of 24 lanes, one per sum of a record
     __shared__ uint64_t wv[kWaves][kOutWords + 1];   // each wave's additive words (+ flips)
-    __shared__ double wd[kWaves][8];                 // six sums, max_abs, max_rel
+    __shared__ double ws[kGroups][kWaves * 6];       // each group's sums
+    __shared__ double wd[kWaves][2];                 // max_abs, max_rel
     __shared__ int64_t wi[kWaves][4];                // argmax_abs, argmax_rel, argmax_ulp, first NaN
     __shared__ uint64_t wmu[kWaves];
     // kBlock records (152 KiB of the 160 KiB of LDS of a gfx950 workgroup)
     __shared__ u32x4 stage[kBlock * kRecParts];
 
-    FinAcc A;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) A.s[k] = 0.0;
-    A.ma = A.mr = -1.0;
-    A.ia = A.ir = A.iu = -1;
-    A.fn = ~uint64_t(0);
-    A.mu = A.sulp = A.flips = 0;
-#pragma unroll
-    for (int k = 0; k < kCnt + PEAT_MAX_THRESHOLDS; ++k) A.cn[k] = 0;
-    // The pair's records go to LDS kBlock at a time in one coalesced copy (a
-    // thread reading its own record from memory would touch a different
-    // cache line in every lane of a load, more lines than the L1 holds);
-    // thread t then merges record t of the batch, and wave w sums the
-    // histogram rows of records w, w + 4, ...: lane l slot l, and lane l < 63
-    // the tail slot 64 + l % 3 of records l / 3 + 21 j (every record and tail
-    // slot once).
-    uint64_t h0 = 0, ht = 0;
+    double ma = -1.0, mr = -1.0;
+    int64_t ia = -1, ir = -1, iu = -1;
+    uint64_t fn = ~uint64_t(0), mu = 0, sulp = 0, flips = 0;
+    // The pair's records go to LDS kBlock at a time in one coalesced copy.
+    // Then thread t takes the maxima of record t of the batch; wave w adds the
+    // additive words of records w, w + 4, ..., lane l words l and 64 + l; and
+    // lane l of the wave adds sum l % 24 of the chunks of group 2w + l / 24
+    // (chunk c of the pair belongs to group c % 8).
+    uint64_t a0 = 0, a1 = 0;
+    double acc = 0.0;
     const ChunkPartial *srec = reinterpret_cast<const ChunkPartial *>(stage);
-    const int tr = lane / 3, tslot = 64 + lane % 3;
+    const int grp = 2 * wave + (lane >= 24 ? 1 : 0), fld = lane % 24;
     for (int base = 0; base < m; base += kBlock) {   // uniform
         const int cnt = min(m - base, kBlock);
         // all parts in flight at once: buffer loads from one scalar base; a
@@ -236,108 +139,106 @@ __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(parts + base), (short)0, cnt * (int)sizeof(ChunkPartial), kBufFlags);
         const int lim = cnt * kRecParts - 1;
+        // (few records: the loads that all lanes would clamp are left out)
+        constexpr int kHalf = kRecParts / 2;
         u32x4 v[kRecParts];
 #pragma unroll
-        for (int k = 0; k < kRecParts; ++k)
+        for (int k = 0; k < kHalf; ++k)
             v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, min(tid + k * kBlock, lim) * 16, 0, 0);
+        const bool full = lim >= kHalf * kBlock;      // uniform
+        if (full) {
+#pragma unroll
+            for (int k = kHalf; k < kRecParts; ++k)
+                v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, min(tid + k * kBlock, lim) * 16, 0, 0);
+        }
         // (the scheduler would otherwise pair each load with its store and
         // wait for it, one round trip per part)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int k = 0; k < kRecParts; ++k) stage[tid + k * kBlock] = v[k];
+        for (int k = 0; k < kHalf; ++k) stage[tid + k * kBlock] = v[k];
+        if (full) {
+#pragma unroll
+            for (int k = kHalf; k < kRecParts; ++k) stage[tid + k * kBlock] = v[k];
+        }
         __syncthreads();
-        if (!split) {
-            const RecF r = load_rec(srec[min(tid, cnt - 1)]);
-            fin_sums(A, r.s, tid < cnt);
-            fin_merge(A, r, tid < cnt);
-        } else {
-            // chunk c of the pair belongs to thread c % kBlock, as above: the
-            // batch's chunks to one wave
-            static_assert(kBlock >> kPieceLog2 == 64, "a batch of records is one wave of chunks");
-            const int r0 = lane << kPieceLog2;
-            if (wave == ((base / kBlock) & (kWaves - 1)) && r0 < cnt) {
-                double s[kWaves][6];
-#pragma unroll 1
-                for (int j = 0; j < 1 << kPieceLog2 && r0 + j < cnt; ++j) {
-                    const RecF r = load_rec(srec[r0 + j]);
-#pragma unroll
-                    for (int w = 0; w < kWaves; ++w)
-#pragma unroll
-                        for (int k = 0; k < 6; ++k) s[w][k] = j == 0 ? r.s[w][k] : s[w][k] + r.s[w][k];
-                    fin_merge(A, r, true);
-                }
-                fin_sums(A, s, true);
-            }
+        {
+            const ChunkPartial &r = srec[min(tid, cnt - 1)];
+            const bool e = tid < cnt && r.run_end != 0;     // else: no exact fields
+            lex_take(ma, ia, r.max_abs, e ? r.ix_abs : int64_t(-1));
+            lex_take(mr, ir, r.max_rel, e ? r.ix_rel : int64_t(-1));
+            lex_take(mu, iu, (uint64_t)r.max_ulp, e ? r.ix_ulp : int64_t(-1));
+            fn = (e && r.first_nan >= 0 && (uint64_t)r.first_nan < fn) ? (uint64_t)r.first_nan : fn;
+            sulp += e ? r.sum_ulp : 0u;
+            flips += tid < cnt ? r.flips : 0u;
         }
-        // bit u: record wave + 4u exists and ends a run (only those rows were written)
+        // bit u: record wave + 4u exists and ends a run (only those were
+        // written; the others' words in LDS are whatever was there)
         const uint64_t em = __ballot(wave + lane * kWaves < cnt && srec[min(wave + lane * kWaves, cnt - 1)].run_end != 0);
-#pragma unroll
-        for (int u = 0; u < 64; ++u) {
-            const uint32_t x = srec[min(wave + u * kWaves, cnt - 1)].hist[lane];
-            h0 += ((em >> u) & 1u) ? x : 0u;
+        const int rounds = (cnt + kWaves - 1) / kWaves;     // uniform, up to 64
+        uint32_t x0 = 0, x1 = 0;                            // below 2^32: at most 64 runs of 2^21 elements
+#pragma unroll 8
+        for (int u = 0; u < rounds; ++u) {
+            const uint32_t *w = srec[wave + u * kWaves].cnt;
+            const uint32_t y0 = w[lane], y1 = w[min(64 + lane, kAdd - 1)];
+            x0 += ((em >> u) & 1u) ? y0 : 0u;
+            x1 += ((em >> u) & 1u) ? y1 : 0u;
         }
+        a0 += x0;
+        a1 += x1;
+        if (!split) {
+#pragma unroll 8
+            for (int i = 0; i < kBlock / kGroups; ++i) {
+                const int c = grp + i * kGroups;
+                const double x = (&srec[c].s[0][0])[fld];
+                // the sum starts at +0 and never becomes -0, so adding +0 is exact
+                acc += c < cnt ? x : 0.0;
+            }
+        } else {
+            // the pieces of a chunk first, in order, as the chunk pass adds them
+            static_assert((kBlock >> kPieceLog2) % kGroups == 0, "a batch's chunks begin at group 0");
+#pragma unroll 2
+            for (int i = 0; i < (kBlock >> kPieceLog2) / kGroups; ++i) {
+                const int r = (grp + i * kGroups) << kPieceLog2;
+                double x = (&srec[r].s[0][0])[fld];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = tr + 21 * j;
-            const uint32_t x = srec[min(wave + min(r, 63) * kWaves, cnt - 1)].hist[tslot];
-            ht += (lane < 63 && r < 64 && ((em >> r) & 1u)) ? x : 0u;
+                for (int j = 1; j < 1 << kPieceLog2; ++j) {
+                    const double y = (&srec[r + j].s[0][0])[fld];
+                    x = r + j < cnt ? x + y : x;
+                }
+                acc += r < cnt ? x : 0.0;
+            }
         }
         __syncthreads();                            // the stage is free again
     }
-
-    // wave totals
-    // up to this bound a wave's records (at most m / 4 chunks of 2^18
-    // elements) count fewer than 2^31 elements
-    const bool small = m <= kBlock * 64;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) A.s[k] = dpp_sum(A.s[k]);
-    fin_step<kDppXor1, 0xF>(A);
-    fin_step<kDppXor2, 0xF>(A);
-    fin_step<kDppHalfMirror, 0xF>(A);
-    fin_step<kDppMirror, 0xF>(A);
-    fin_step<kDppBcast15, 0xA>(A);
-    fin_step<kDppBcast31, 0xC>(A);
-    uint64_t vals[kTot], tot[kTot];
-#pragma unroll
-    for (int k = 0; k < kCnt + PEAT_MAX_THRESHOLDS; ++k) vals[k] = A.cn[k];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) vals[kCnt + PEAT_MAX_THRESHOLDS + q] = lane % 3 == q ? ht : 0u;
-    wave_totals(vals, tot, small);
-    const uint64_t t0 = tot[kTot - 3], t1 = tot[kTot - 2], t2 = tot[kTot - 1];
-    // ULP sum in two 32-bit halves (each wave total below 2^38: exact)
-    const uint64_t sulp = ((uint64_t)dpp_sum((double)(A.sulp >> 32)) << 32) +
-                          (uint64_t)dpp_sum((double)(A.sulp & 0xFFFFFFFFu));
-    const uint64_t flips = P.inj_counts ? (uint64_t)dpp_sum((double)A.flips) : 0u;
-
-    // this wave's additive words by output word: lane l slot l (lanes 0-2 the
-    // tail slots too), lanes 0-15 the counts, 16 the ULP sum, 17 the flips
+    // the wave's maxima (every lane gets them) and integer sums
+#pragma unroll 1
+    for (int o = 32; o >= 1; o >>= 1) {
+        const double oma = __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(ma), o));
+        const double omr = __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(mr), o));
+        const uint64_t omu = shfl_xor_u64(mu, o), ofn = shfl_xor_u64(fn, o);
+        const int64_t oia = (int64_t)shfl_xor_u64((uint64_t)ia, o), oir = (int64_t)shfl_xor_u64((uint64_t)ir, o);
+        const int64_t oiu = (int64_t)shfl_xor_u64((uint64_t)iu, o);
+        sulp += shfl_xor_u64(sulp, o);
+        flips += shfl_xor_u64(flips, o);
+        lex_take(ma, ia, oma, oia);
+        lex_take(mr, ir, omr, oir);
+        lex_take(mu, iu, omu, oiu);
+        fn = ofn < fn ? ofn : fn;
+    }
     uint64_t *row = wv[wave];
-    row[slot_word(lane, nb)] = h0;
-    uint64_t v = 0;
-#pragma unroll
-    for (int k = 0; k < kCnt + PEAT_MAX_THRESHOLDS; ++k) v = lane == k ? tot[k] : v;
-    v = lane == 16 ? sulp : (lane == 17 ? flips : v);
-    const int vw = lane < kCnt ? kW_cnt + lane
-                               : (lane < 16 ? kW_mism + lane - kCnt : (lane == 16 ? kW_sumulp : kOutWords));
-    if (lane < 18) row[vw] = v;
-    if (lane < 3) row[slot_word(64 + lane, nb)] = lane == 0 ? t0 : (lane == 1 ? t1 : t2);
-    // the reductions' results, read from lane 63 by every lane: a lane read
-    // inside the branch below would let the compiler move the last step's
-    // selects into it, where lane 63 does not execute them
-    const double wma = lane63_f64(A.ma), wmr = lane63_f64(A.mr);
-    const int64_t wia = (int64_t)lane63_u64((uint64_t)A.ia), wir = (int64_t)lane63_u64((uint64_t)A.ir);
-    const int64_t wiu = (int64_t)lane63_u64((uint64_t)A.iu), wfn = (int64_t)lane63_u64(A.fn);  // ~0 is -1
-    const uint64_t wmuv = lane63_u64(A.mu);
+    row[add_word(lane, nb)] = a0;
+    if (lane < kAdd - 64) row[add_word(64 + lane, nb)] = a1;
+    if (lane < 48) ws[grp][fld] = acc;
     if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) wd[wave][k] = A.s[k];
-        wd[wave][6] = wma;
-        wd[wave][7] = wmr;
-        wi[wave][0] = wia;
-        wi[wave][1] = wir;
-        wi[wave][2] = wiu;
-        wi[wave][3] = wfn;
-        wmu[wave] = wmuv;
+        row[kW_sumulp] = sulp;
+        row[kOutWords] = flips;
+        wd[wave][0] = ma;
+        wd[wave][1] = mr;
+        wi[wave][0] = ia;
+        wi[wave][1] = ir;
+        wi[wave][2] = iu;
+        wi[wave][3] = (int64_t)fn;                   // ~0 is -1
+        wmu[wave] = mu;
     }
     __syncthreads();
 
@@ -354,9 +255,12 @@ __global__ void __launch_bounds__(kBlock) sig_finalize(SigParams P) {
     for (int w = 0; w < kWaves; ++w) {
         add += wv[w][t];
         nanp += wv[w][kW_cnt + C_NANPAIR];
-        S += wd[w][ks];
-        lex_take(MA, IA, wd[w][6], wi[w][0]);
-        lex_take(MR, IR, wd[w][7], wi[w][1]);
+        double sg = ws[0][w * 6 + ks];
+#pragma unroll
+        for (int g = 1; g < kGroups; ++g) sg += ws[g][w * 6 + ks];
+        S += sg;
+        lex_take(MA, IA, wd[w][0], wi[w][0]);
+        lex_take(MR, IR, wd[w][1], wi[w][1]);
         lex_take(MU, IU, wmu[w], wi[w][2]);
         const uint64_t x = (uint64_t)wi[w][3];     // -1 (none) is the largest
         FN = x < FN ? x : FN;
