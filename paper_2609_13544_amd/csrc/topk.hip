@@ -35,12 +35,14 @@
 //
 // What bounds it: HBM for the gather (6.2 TB/s on 54 f32 tensors of a
 // Llama-shaped checkpoint with Adam moments, 9.7 GB; 6.1 TB/s on 16 rectified
-// f32 [8, 512, 4096] pairs), latency for start and resolve (21 and 28 us for
-// one f32 [1024, 1024] pair, 40 and 29 us for 54 pairs).  Before -- the window
+// f32 [8, 512, 4096] pairs), latency for start and resolve (21 and 19 us for
+// one f32 [1024, 1024] pair, 40 and 21 us for 54 pairs; resolve took 28 and 29
+// with 4096 keys in LDS, too few for the pair's, and every bin's keys ranked,
+// also when they were one key listed by many chunks).  Before -- the window
 // a whole binade, gathered by a wave-wide look at every element, its order
 // found by a histogram and a selection kernel per 13 bits, a second pass over
 // the tensors where a binade holds many distinct errors -- the same three took
-// 2000, 1150 and 380 us a call; now 1646, 440 and 90.
+// 2000, 1150 and 380 us a call; now 1598, 440 and 63.
 #include "elements.h"
 
 namespace peat {
@@ -852,13 +854,13 @@ __global__ void __launch_bounds__(kBlock) topk_gather(TopkParams P) {
 }
 
 // ---- resolve -----------------------------------------------------------------------
-constexpr int kCache = 4096;                    // gathered keys kept in LDS after the first pass over them
+constexpr int kCache = 8192;                    // gathered keys kept in LDS after the first pass over them
 struct ResolveShared {
     unsigned long long h[kRelBins];
     uint64_t ckey[kCache];
-    uint64_t ccnt[kCache];
     uint64_t lkey[kList];
-    uint64_t lcnt[kList];
+    uint32_t ccnt[kCache];                      // (a gathered key's copies lie in one chunk)
+    uint32_t lcnt[kList];
     Sel sel;
     double red[kBigWaves];
     uint32_t ncache, nlist;
@@ -961,7 +963,7 @@ __global__ void __launch_bounds__(kBig) topk_resolve(TopkParams P) {
         bool cached = false;                                  // the gathered keys are in LDS
         auto for_each_key = [&](auto &&f) {
             if (cached)
-                for (uint32_t i = tid; i < sh.ncache; i += kBig) f(sh.ckey[i], sh.ccnt[i]);
+                for (uint32_t i = tid; i < sh.ncache; i += kBig) f(sh.ckey[i], (uint64_t)sh.ccnt[i]);
             else
                 for_each_gathered(P, d, f);
         };
@@ -978,7 +980,7 @@ __global__ void __launch_bounds__(kBig) topk_resolve(TopkParams P) {
                     const uint32_t q = atomicAdd(&sh.ncache, 1u);
                     if (q < kCache) {
                         sh.ckey[q] = key;
-                        sh.ccnt[q] = n;
+                        sh.ccnt[q] = (uint32_t)n;
                     }
                 }
             });
@@ -1007,15 +1009,22 @@ __global__ void __launch_bounds__(kBig) topk_resolve(TopkParams P) {
                     const uint32_t q = atomicAdd(&sh.nlist, 1u);
                     if (q < kList) {
                         sh.lkey[q] = key;
-                        sh.lcnt[q] = n;
+                        sh.lcnt[q] = (uint32_t)n;
                     }
                 }
             });
             __syncthreads();
             const uint32_t m = sh.nlist;
             if (m <= kList) {
-                // the listed keys' ranks
-                if ((uint32_t)tid < m) {
+                // one key, listed by many chunks (errors that repeat), or the
+                // listed keys' ranks
+                const uint64_t one = sh.lkey[0];
+                if (__syncthreads_and((uint32_t)tid >= m || sh.lkey[tid] == one)) {
+                    if (tid == 0) {
+                        sh.T = one;
+                        sh.need = need;
+                    }
+                } else if ((uint32_t)tid < m) {
                     const uint64_t mykey = sh.lkey[tid];
                     uint64_t gt = 0, ge = 0;
                     for (uint32_t q = 0; q < m; ++q) {
