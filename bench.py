@@ -284,15 +284,15 @@ def cpu_baseline(wl: Workload, threads: int, target_bytes: float = 12e9):
 
 def topk_measure(torch, P, prep_pairs, nbytes: int, reps: int = 3):
     """The paper's main score, the mean of the top 10% errors, over every pair
-    of the workload: peat_topk_mean_batched (a sampled guess of each pair's
-    boundary binade, the gathering pass that confirms it, the binade pass
-    only where a guess fails, and the rounds), and the stream-ordered
-    peat_topk_mean_from_signature_batched_async fed with the device records
-    of the step's signature call on the same stream (the binade pass skips
-    every pair whose record bounds the k-th largest error to one bin; the
-    gathering pass collects that bin's range).  Best of
-    reps from the library's kernel events: level 0 (class K_TOPK_A) and the
-    rest (K_TOPK_B); nothing in either waits on the host."""
+    of the workload: peat_topk_mean_batched (a sampled window of each pair's
+    errors, one gathering pass that confirms it, the selection among the
+    gathered errors, and passes digit by digit only where a window fails), and
+    the stream-ordered peat_topk_mean_from_signature_batched_async fed with
+    the device records of the step's signature call on the same stream (the
+    same steps, the passes digit by digit enqueued as well: they return at
+    once where no window failed).  Best of
+    reps from the library's kernel events: the sampling (class K_TOPK_A) and
+    the rest (K_TOPK_B)."""
     def timed(call):
         call()                                                   # warm-up
         P.profile_enable(True)
@@ -317,8 +317,7 @@ def topk_measure(torch, P, prep_pairs, nbytes: int, reps: int = 3):
     d_top = torch.empty(count * P.TOPK_BYTES, dtype=torch.uint8, device="cuda")
     slvl0, srest = timed(lambda: P.topk_mean_from_signature_batched_async(prep_pairs, d_sig, d_top, num=1, den=10))
     recs_s = P.decode_topk(d_top, count)
-    # exact fields identical; sums identical where the record fixes the
-    # boundary's binade, else formed per binade (within 1e-12 relative)
+    # every field is expected to be identical; the sums' difference is reported
     same = all(x[f] == y[f] or (x[f] != x[f] and y[f] != y[f]) for x, y in zip(recs, recs_s)
                for f in ("n_valid", "k", "count_above", "kth_value"))
     rel = max((abs(x["sum_topk"] - y["sum_topk"]) / abs(y["sum_topk"]) if y["sum_topk"] not in (0.0, float("inf"))

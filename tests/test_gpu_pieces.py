@@ -39,3 +39,19 @@ def test_pieces(n, code, frac):
         torch.cuda.synchronize()
         for rec in P.decode_records(d_out, count, nthr=len(synth.THRESHOLDS)):
             assert repr(rec) == repr(lone)
+
+
+@pytest.mark.parametrize("n,code", [(M, 1), (M + (1 << 16) + 4097, 0), (4 * M + 1, 2)])
+def test_pieces_with_injection(n, code):
+    """The one-pass step with its pieces apart: flips, counts and records of the
+    two separate calls."""
+    gb, tb = special_pair(n, code, seed=n, special_frac=1e-5)
+    g, t, u = to_device(gb, code), to_device(tb, code), to_device(tb, code)
+    d_out = torch.zeros(P.SIG_BYTES, dtype=torch.uint8, device="cuda")
+    d_counts = torch.zeros(1, dtype=torch.int64, device="cuda")
+    P.inject_signature_batched_async([(g, t)], [11], 1e-5, 1 << 9, d_out, d_counts, synth.BINS, synth.THRESHOLDS)
+    flips = P.inject(u, 11, 1e-5, 1 << 9)
+    torch.cuda.synchronize()
+    assert flips > 0 and int(d_counts.item()) == flips and torch.equal(t.view(torch.uint8), u.view(torch.uint8))
+    rec = P.decode_records(d_out, 1, nthr=len(synth.THRESHOLDS))[0]
+    assert repr(rec) == repr(P.signature(g, u, synth.BINS, synth.THRESHOLDS))
