@@ -247,7 +247,8 @@ int peat_signature_batched_async(const peat_pair_t *pairs, int32_t count,
  * PEAT_NOALLOC_SCRATCH_BYTES that every GPU the library runs on holds until
  * the process ends.  A pair of n elements has ceil(n / C) chunks, C the
  * smallest power of two in [2^12, 2^18] that is at least n / 256 (n < 2^22)
- * or n / 64 (n >= 2^22).  The call makes no device, pinned or host-heap
+ * or n / 64 (n >= 2^22); a call of at most 1536 chunks and as many pairs may
+ * use four records for each, which always fit.  The call makes no device, pinned or host-heap
  * allocation; the device's one-time set-up does (events, the array's
  * address), so call peat_init() on each device first when that matters.
  * pairs is host memory read before the call returns (descriptors travel as

@@ -47,7 +47,7 @@ inline int chunk_log2_for(int64_t n) {
 // rounds of the 768 blocks that the chip holds (784 chunks of 2^17 left 752
 // of them idle in the second), and, of one pair, up to kSplitPairChunks, which
 // is four rounds of the pair's finalize block.  A lone pair of 2^24 binary16
-// elements (64 chunks) took 72.5 us, 48 of them in the chunk pass, and now takes 53.3
+// elements (64 chunks) took 72.5 us, 48 of them in the chunk pass, and now takes 52
 // (27 in the chunk pass); 16 pairs of 6.4 M bf16 elements (784 chunks) 202 -> 193.
 // In larger calls the pieces cost nothing measurable (0.0 to 0.2 %).
 constexpr int kPieceLog2 = 2;
